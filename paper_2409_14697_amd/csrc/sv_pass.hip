@@ -123,6 +123,26 @@ __device__ __forceinline__ T cload(cptr<T> p) {
   return out;
 }
 
+// The head of a stage descriptor in scalar registers (one burst of loads; the
+// store map's columns and the earlier layers are read where they are needed).
+struct StageHead {
+  uint32_t w[offsetof(PassStageDev, colimg) / 4];
+};
+static_assert(offsetof(PassStageDev, q) == 0, "q leads the head");
+struct Stage {
+  StageHead h;
+  cptr<PassStageDev> p;
+#define SV_HEAD(NAME) \
+  __device__ __forceinline__ uint32_t NAME() const { return h.w[offsetof(PassStageDev, NAME) / 4]; }
+  SV_HEAD(form) SV_HEAD(flags) SV_HEAD(slots) SV_HEAD(u2) SV_HEAD(dr) SV_HEAD(item_first) SV_HEAD(item_count)
+  SV_HEAD(px_first) SV_HEAD(px_count) SV_HEAD(mat_base) SV_HEAD(rows) SV_HEAD(row_count) SV_HEAD(pconst)
+  SV_HEAD(slot_mask) SV_HEAD(nsub)
+#undef SV_HEAD
+  __device__ __forceinline__ uint32_t q(int b) const { return h.w[b]; }
+  __device__ __forceinline__ uint32_t qsort(int b) const { return h.w[offsetof(PassStageDev, qsort) / 4 + b]; }
+};
+__device__ __forceinline__ Stage load_stage(cptr<PassStageDev> p) { return {cload((cptr<StageHead>)p), p}; }
+
 // ---- the 2x2 part: one gate per register bit, in the stage's form ----------
 // Each applies the 2x2 at M[0..3] to every pair of register amplitudes that
 // differ in bit B (Eq. 2 on the register bits).
@@ -335,12 +355,13 @@ struct pre_cap {
 // with a barrier).  Each thread sums whole rows: its 34 tile words are
 // independent loads, so they are in flight together.
 template <typename R>
-__device__ __forceinline__ void stage_rows(const PassStageDev& S, cptr<cplx<R>> mats, uint64_t base,
+__device__ __forceinline__ void stage_rows(const Stage& S, cptr<cplx<R>> mats, uint64_t base,
                                            typename lp_word<R>::W* ts) {
   typedef typename lp_word<R>::W W;
-  const cptr<cplx<R>> sm = mats + S.mat_base;
-  const cptr<uint32_t> rt = (cptr<uint32_t>)(sm + S.rows);
-  for (uint32_t j = threadIdx.x; j < S.row_count; j += kBlock) {
+  const cptr<cplx<R>> sm = mats + S.mat_base();
+  const cptr<uint32_t> rt = (cptr<uint32_t>)(sm + S.rows());
+  const uint32_t rows = S.row_count();
+  for (uint32_t j = threadIdx.x; j < rows; j += kBlock) {
     const uint32_t word = rt[4 * j], pred = rt[4 * j + 1];
     const uint64_t sel = base & (rt[4 * j + 2] | ((uint64_t)rt[4 * j + 3] << 32));
     const cptr<W> w = (cptr<W>)sm + word;
@@ -387,7 +408,7 @@ __device__ __forceinline__ cplx<R> pick(cptr<cplx<R>> T, uint32_t var, int n) {
 // and, per register bit a, factors f0[a] / f1[a] on the amplitudes whose bit
 // a is 0 / 1; amplitude r is multiplied by G * prod_a f_{r_a}[a] * dr[r].
 template <typename R, bool LP>
-__device__ __forceinline__ void lane_diag(const PassStageDev& S, cptr<PassItemDev> items, cptr<cplx<R>> mats,
+__device__ __forceinline__ void lane_diag(const Stage& S, cptr<PassItemDev> items, cptr<cplx<R>> mats,
                                           uint32_t xg, uint64_t base, const typename lp_word<R>::W* ts,
                                           const typename lp_word<R>::W* pre, uint32_t npre, uint32_t* kfix,
                                           cplx<R>* v) {
@@ -398,8 +419,10 @@ __device__ __forceinline__ void lane_diag(const PassStageDev& S, cptr<PassItemDe
 #pragma unroll
   for (int b = 0; b < RB; ++b) f0[b] = f1[b] = one;
   uint32_t row = 0;  // the item's first row in ts
-  for (uint32_t i = 0; i < S.item_count; ++i) {
-    const PassItemDev it = cload(items + (S.item_first + i));
+  const cptr<PassItemDev> ip = items + S.item_first();
+  const uint32_t n_items = S.item_count();
+  for (uint32_t i = 0; i < n_items; ++i) {
+    const PassItemDev it = cload(ip + i);
     const cptr<cplx<R>> T = mats + it.mat;
     if (it.type == PIT_DG) {
       const uint32_t sb = (it.sel >> 8) & 0xffu;
@@ -431,7 +454,7 @@ __device__ __forceinline__ void lane_diag(const PassStageDev& S, cptr<PassItemDe
   // factors of the register index over the bits below the top one, by doubling
   cplx<R> H[HALF];
   H[0] = G;
-  if (S.flags & PSF_F0) {
+  if (S.flags() & PSF_F0) {
 #pragma unroll
     for (int a = 0; a < RB - 1; ++a)
 #pragma unroll
@@ -445,7 +468,7 @@ __device__ __forceinline__ void lane_diag(const PassStageDev& S, cptr<PassItemDe
 #pragma unroll
       for (int k = 0; k < (1 << a); ++k) H[k | (1 << a)] = cmul(H[k], f1[a]);
   }
-  const cptr<cplx<R>> D = mats + S.dr;
+  const cptr<cplx<R>> D = mats + S.dr();
 #pragma unroll
   for (int r = 0; r < HALF; ++r) {
     const cplx<R> lo = cmul(cmul(H[r], f0[RB - 1]), cget(D, r));
@@ -513,12 +536,13 @@ struct TileThreads {
 struct LaneGeo {
   uint32_t per;
   bool on;
+  bool full;  // a 64 KiB tile: every lane moves BATCH elements
 };
 
 template <int LB, int NT = kBlock>
 __device__ __forceinline__ LaneGeo lane_geo(uint32_t m) {
   const uint32_t elems = (1u << m) >> LB;
-  return {elems >= (uint32_t)NT ? elems / NT : 1u, threadIdx.x < elems};
+  return {elems >= (uint32_t)NT ? elems / NT : 1u, threadIdx.x < elems, elems == 4096u};
 }
 
 // Physical offset of element slot bit i when the load fills slot e with tile
@@ -563,28 +587,32 @@ __device__ __forceinline__ void tile_load_lds(const TileRef<R>& T, typename dev_
   // the instruction is wave-uniform; lanes land at consecutive 16 bytes)
   const uint32_t wslot = (threadIdx.x & ~63u);
   __attribute__((address_space(3))) G* lds = (__attribute__((address_space(3))) G*)tile;
+  auto move = [&](uint32_t u) {
+    uint64_t ad = a0;
 #pragma unroll
-  for (int u = 0; u < kBatch; ++u)
-    if ((uint32_t)u < lg.per && lg.on) {
-      uint64_t ad = a0;
+    for (int b = 0; b < 4; ++b)
+      if ((u >> b) & 1) ad ^= hb[b];
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(gpsi + (ad >> LB)),
+                                     (__attribute__((address_space(3))) void*)(lds + wslot + u * kBlock), 16, 0, 0);
+  };
+  if (lg.full) {
 #pragma unroll
-      for (int b = 0; b < 4; ++b)
-        if ((u >> b) & 1) ad ^= hb[b];
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(gpsi + (ad >> LB)),
-                                       (__attribute__((address_space(3))) void*)(lds + wslot + u * kBlock), 16, 0,
-                                       0);
-    }
+    for (int u = 0; u < kBatch; ++u) move(u);
+  } else if (lg.on) {
+#pragma unroll 1
+    for (uint32_t u = 0; u < lg.per; ++u) move(u);
+  }
 }
 
 // The pass's register stages on the tile in LDS (ends with a barrier).
 // The lane's group index in a stage: thread t's group with zeros inserted at
 // the register bits (ascending positions qsort).
 template <int RB>
-__device__ __forceinline__ uint32_t group_bits(uint32_t gi, const uint32_t* qsort) {
+__device__ __forceinline__ uint32_t group_bits(uint32_t gi, const Stage& S) {
   uint32_t xg = gi;
 #pragma unroll
   for (int b = 0; b < RB; ++b) {
-    const uint32_t q = qsort[b];
+    const uint32_t q = S.qsort(b);
     xg = ((xg >> q) << (q + 1)) | (xg & ((1u << q) - 1u));
   }
   return xg;
@@ -600,11 +628,11 @@ __device__ __forceinline__ uint32_t pre_fill(cptr<PassDescDev> P, cptr<PassStage
   const uint32_t groups = (1u << P->m) >> RB, t = threadIdx.x;
   uint32_t k = 0;
   for (uint32_t si = 0; si < P->stage_count && k < cap; ++si) {
-    const PassStageDev S = cload(stages + (P->stage_first + si));
-    if (!(S.flags & PSF_LANE)) continue;
-    const uint32_t xg = group_bits<RB>(t, S.qsort);
-    for (uint32_t i = 0; i < S.item_count && k < cap; ++i) {
-      const PassItemDev it = cload(items + (S.item_first + i));
+    const Stage S = load_stage(stages + (P->stage_first + si));
+    if (!(S.flags() & PSF_LANE)) continue;
+    const uint32_t xg = group_bits<RB>(t, S), n_items = S.item_count(), first = S.item_first();
+    for (uint32_t i = 0; i < n_items && k < cap; ++i) {
+      const PassItemDev it = cload(items + (first + i));
       if (it.type != PIT_LP && it.type != PIT_QG) continue;
       if (t < groups)
         pre[k * kBlock + t] = it.type == PIT_LP ? lp_lane_part<R>(it, mats + it.mat, xg)
@@ -632,9 +660,10 @@ __device__ __forceinline__ void tile_stages(const TileRef<R>& T, typename dev_el
   __shared__ W tsum[LP ? kPassStageRowsMax : 1];  // tile sums of the stage's fixed-point rows
   uint32_t kfix = 0;  // fixed-point phase items of the pass so far
   for (uint32_t si = 0; si < P->stage_count; ++si) {
-    const PassStageDev S = cload(stages + (P->stage_first + si));
+    const Stage S = load_stage(stages + (P->stage_first + si));
+    const uint32_t flags = S.flags();
     if constexpr (LP) {
-      if (S.row_count) stage_rows<R>(S, mats, base, tsum);
+      if (S.row_count()) stage_rows<R>(S, mats, base, tsum);
     }
     const uint32_t groups = size >> RB;
     // swz is linear over XOR and xg shares no bit with a register offset, so
@@ -642,36 +671,36 @@ __device__ __forceinline__ void tile_stages(const TileRef<R>& T, typename dev_el
     // the swizzled register bits are kept, not one offset per register
     uint32_t sbit[RB], cbit[RB];
 #pragma unroll
-    for (int b = 0; b < RB; ++b) sbit[b] = swz<LB>(1u << S.q[b]);
+    for (int b = 0; b < RB; ++b) sbit[b] = swz<LB>(1u << S.q(b));
     // the store writes local index x to M x ^ c: register bit j of an
     // amplitude moves its address by the swizzled image of column q[j]
 #pragma unroll
     for (int j = 0; j < RB; ++j) {
-      uint32_t img = 0;
-#pragma unroll
-      for (int l = 0; l < kPassLocalMax; ++l) img = (uint32_t)l == S.q[j] ? S.colimg[l] : img;
+      uint32_t img = 1u << S.q(j);
+      if (flags & PSF_PERM) img = S.p->colimg[S.q(j)];
       cbit[j] = __builtin_amdgcn_readfirstlane(swz<LB>(img));
     }
     // the constant of the map for this tile (the terms selected by tile bits)
-    uint32_t cmap = S.pconst;
-    for (uint32_t k = 0; k < S.px_count; ++k) {
-      const PassItemDev it = cload(items + (S.px_first + k));
+    uint32_t cmap = S.pconst();
+    for (uint32_t k = 0; k < S.px_count(); ++k) {
+      const PassItemDev it = cload(items + (S.px_first() + k));
       if (sel_bit(it.sel & 0xffu, 0u, base)) cmap ^= it.a;
     }
-    const bool xperm = (S.flags & PSF_XPERM) != 0;
+    const bool xperm = (flags & PSF_XPERM) != 0;
     // fixed-point items of this stage (every group of the stage walks them)
     uint32_t nfix = 0;
     if constexpr (LP) {
-      if (S.flags & PSF_LANE)
-        for (uint32_t i = 0; i < S.item_count; ++i) {
-          const uint32_t ty = items[S.item_first + i].type;
+      if (flags & PSF_LANE)
+        for (uint32_t i = 0; i < S.item_count(); ++i) {
+          const uint32_t ty = items[S.item_first() + i].type;
           nfix += ty == PIT_LP || ty == PIT_QG;
         }
     }
     // a tile holds at most kBlock groups: one per thread
     const bool own = t < groups;
     {
-      const uint32_t xg = own ? group_bits<RB>(t, S.qsort) : 0u;
+      // lanes without a group read group 0 (and store nothing)
+      const uint32_t xg = own ? group_bits<RB>(t, S) : 0u;
       const uint32_t sx = swz<LB>(xg);
       cplx<R> v[NR];
 #pragma unroll
@@ -680,17 +709,16 @@ __device__ __forceinline__ void tile_stages(const TileRef<R>& T, typename dev_el
 #pragma unroll
         for (int b = 0; b < RB; ++b)
           if ((r >> b) & 1) o ^= sbit[b];
-        const E e = own ? tile[o] : E{};
+        const E e = tile[o];
         v[r] = cplx<R>{e.x, e.y};
       }
-      if (S.flags & PSF_U2) op_u2<R>(v, mats + S.u2);
+      if (flags & PSF_U2) op_u2<R>(v, mats + S.u2());
       // the earlier layers (2x2s, then register factors), then the last one;
       // one copy of the layer code serves all of them
-      const cptr<PassSubDev> subs = (cptr<PassSubDev>)((cptr<uint32_t>)(stages + (P->stage_first + si)) +
-                                                      offsetof(PassStageDev, sub) / 4);
-      for (uint32_t li = 0; li <= S.nsub; ++li) {
-        const bool last = li == S.nsub;
-        const PassSubDev L = last ? PassSubDev{S.form, S.slot_mask, S.slots, kPassNoTable} : cload(subs + li);
+      const cptr<PassSubDev> subs = (cptr<PassSubDev>)((cptr<uint32_t>)S.p + offsetof(PassStageDev, sub) / 4);
+      for (uint32_t li = 0; li <= S.nsub(); ++li) {
+        const bool last = li == S.nsub();
+        const PassSubDev L = last ? PassSubDev{S.form(), S.slot_mask(), S.slots(), kPassNoTable} : cload(subs + li);
         if (L.form) layer<R>(v, mats + L.slots, L.form);
         if (L.dr != kPassNoTable) {
           const cptr<cplx<R>> D = mats + L.dr;
@@ -698,21 +726,21 @@ __device__ __forceinline__ void tile_stages(const TileRef<R>& T, typename dev_el
           for (int r = 0; r < NR; ++r) v[r] = cmul(cget(D, r), v[r]);
         }
       }
-      if (S.flags & PSF_LANE) {
+      if (flags & PSF_LANE) {
         uint32_t kf = kfix;
         lane_diag<R, LP>(S, items, mats, xg, base, tsum, pre, npre, &kf, v);
-      } else if (S.flags & PSF_DR) {
-        const cptr<cplx<R>> D = mats + S.dr;
+      } else if (flags & PSF_DR) {
+        const cptr<cplx<R>> D = mats + S.dr();
 #pragma unroll
         for (int r = 0; r < NR; ++r) v[r] = cmul(cget(D, r), v[r]);
       }
       // address of the group's register index 0 after the map: M xg ^ c
       uint32_t so = sx;
-      if (S.flags & PSF_PERM) {
+      if (flags & PSF_PERM) {
         uint32_t y = cmap;
 #pragma unroll
         for (int l = 0; l < kPassLocalMax; ++l)
-          if ((xg >> l) & 1u) y ^= S.colimg[l];
+          if ((xg >> l) & 1u) y ^= S.p->colimg[l];
         so = swz<LB>(y);
       }
       // a map that moves amplitudes between groups writes after every
@@ -723,16 +751,18 @@ __device__ __forceinline__ void tile_stages(const TileRef<R>& T, typename dev_el
       asm volatile("" : "+v"(so));
 #pragma unroll
       for (int b = 0; b < RB; ++b) asm volatile("" : "+s"(cbit[b]));
+      if (own) {
 #pragma unroll
-      for (int r = 0; r < NR; ++r) {
-        E e;
-        e.x = v[r].re;
-        e.y = v[r].im;
-        uint32_t o = so;
+        for (int r = 0; r < NR; ++r) {
+          E e;
+          e.x = v[r].re;
+          e.y = v[r].im;
+          uint32_t o = so;
 #pragma unroll
-        for (int b = 0; b < RB; ++b)
-          if ((r >> b) & 1) o ^= cbit[b];
-        if (own) tile[o] = e;
+          for (int b = 0; b < RB; ++b)
+            if ((r >> b) & 1) o ^= cbit[b];
+          tile[o] = e;
+        }
       }
     }
     kfix += nfix;
@@ -740,95 +770,106 @@ __device__ __forceinline__ void tile_stages(const TileRef<R>& T, typename dev_el
   }
 }
 
-// Read the tile for its store into registers: local bit j goes to physical
-// position wpos[j], a permutation of the positions the tile was loaded from.
-// When the lowest element bits keep their positions lanes walk the tile in
-// load order (element x = t + 256 u); otherwise they walk the destination
-// addresses in the load's order (the same coalesced runs and 16-byte
-// elements whatever the permutation) and gather each element from LDS: the
-// element's k-th address bit holds local bit winv[k].
-template <typename R, int NT = kBlock>
-__device__ __forceinline__ void tile_gather(const TileRef<R>& T, const typename dev_elem<R>::E* tile,
-                                            typename gelem<R>::G* out) {
-  typedef typename dev_elem<R>::E E;
-  typedef typename gelem<R>::G G;
-  typedef TileThreads<NT> TT;
+// The write-back: local bit j goes to physical position wpos[j], a
+// permutation of the positions the tile was loaded from.  When the lowest
+// element bits keep their positions lanes walk the tile in load order
+// (element x = t + 256 u); otherwise they walk the destination addresses in
+// the load's order (the same coalesced runs and 16-byte elements whatever the
+// permutation) and gather each element from LDS: the element's k-th address
+// bit holds local bit winv[k].
+//
+// LDS index (swizzled) of the tile's element u of this lane and, complex64,
+// of the element's second amplitude.
+template <typename R>
+struct GatherMap {
+  uint32_t xl, xo[4], xp;
+  bool lane_order;
+};
+template <typename R>
+__device__ __forceinline__ GatherMap<R> gather_map(cptr<PassDescDev> P) {
   constexpr int LB = gelem<R>::LB;
-  const cptr<PassDescDev> P = T.P;
   const uint32_t m = P->m;
-  const LaneGeo lg = lane_geo<LB, NT>(m);
-  // an opaque copy of the thread index: the addresses below are recomputed
-  // per tile instead of being kept live (or spilled) across the whole loop
+  // an opaque copy of the thread index: the addresses are recomputed per
+  // tile instead of being kept live (or spilled) across the whole loop
   uint32_t tid = threadIdx.x;
   asm volatile("" : "+v"(tid));
-  if (P->flags & kPassStoreLaneOrder) {
+  GatherMap<R> g;
+  g.lane_order = (P->flags & kPassStoreLaneOrder) != 0;
+  if (g.lane_order) {
+    g.xl = swz<LB>(tid << LB);
 #pragma unroll
-    for (int u = 0; u < TT::BATCH; ++u)
-      if ((uint32_t)u < lg.per && lg.on) {
-        const uint32_t x = (tid + u * NT) << LB;
-        if constexpr (LB == 1) {
-          // both amplitudes of the element sit in one 16-byte LDS slot
-          out[u] = *reinterpret_cast<const G*>(tile + swz<LB>(x));
-        } else {
-          out[u] = tile[swz<LB>(x)];
-        }
-      }
-    return;
+    for (int b = 0; b < 4; ++b) g.xo[b] = swz<LB>(kBlock << (LB + b));
+    g.xp = 1;
+    return g;
   }
-  // LDS index of the lane's element: lane bit j is address bit LB + j
   uint32_t xl = 0;
-  for (uint32_t jb = 0; jb < (uint32_t)TT::TB && LB + jb < m; ++jb)
-    if ((tid >> jb) & 1u) xl |= 1u << P->winv[LB + jb];
-  uint32_t xo[TT::UB];  // LDS offsets of the batch bits
 #pragma unroll
-  for (int b = 0; b < TT::UB; ++b) {
-    const uint32_t k = LB + TT::TB + b;
-    xo[b] = k < m ? 1u << P->winv[k] : 0u;
+  for (uint32_t jb = 0; jb < 8; ++jb) {
+    const uint32_t w = LB + jb < m ? 1u << P->winv[LB + jb] : 0u;
+    xl |= ((tid >> jb) & 1u) ? w : 0u;
   }
-  const uint32_t xp = LB ? 1u << P->winv[0] : 0u;  // the element's second amplitude (complex64)
+  g.xl = swz<LB>(xl);
 #pragma unroll
-  for (int u = 0; u < TT::BATCH; ++u)
-    if ((uint32_t)u < lg.per && lg.on) {
-      uint32_t x = xl;
+  for (int b = 0; b < 4; ++b) {
+    const uint32_t k = LB + 8 + b;
+    g.xo[b] = k < m ? swz<LB>(1u << P->winv[k]) : 0u;
+  }
+  g.xp = LB ? swz<LB>(1u << P->winv[0]) : 0u;
+  return g;
+}
+template <typename R>
+__device__ __forceinline__ typename gelem<R>::G gather_one(const GatherMap<R>& g, const typename dev_elem<R>::E* tile,
+                                                           uint32_t u) {
+  typedef typename dev_elem<R>::E E;
+  typedef typename gelem<R>::G G;
+  uint32_t x = g.xl;
 #pragma unroll
-      for (int b = 0; b < TT::UB; ++b)
-        if ((u >> b) & 1) x |= xo[b];
-      if constexpr (LB == 1) {
-        const E e0 = tile[swz<LB>(x)], e1 = tile[swz<LB>(x | xp)];
-        out[u] = G{e0.x, e0.y, e1.x, e1.y};
-      } else {
-        out[u] = tile[swz<LB>(x)];
-      }
-    }
+  for (int b = 0; b < 4; ++b)
+    if ((u >> b) & 1) x ^= g.xo[b];
+  if constexpr (gelem<R>::LB == 1) {
+    // in load order both amplitudes of the element sit in one 16-byte slot
+    if (g.lane_order) return *reinterpret_cast<const G*>(tile + x);
+    const E e0 = tile[x], e1 = tile[x ^ g.xp];
+    return G{e0.x, e0.y, e1.x, e1.y};
+  } else {
+    return tile[x];
+  }
 }
 
-// Store the gathered elements: in load order to the wpos addresses of the
-// lane's element, or in destination order to the lpos addresses.
-template <typename R, int NT = kBlock>
-__device__ __forceinline__ void tile_put(const TileRef<R>& T, const typename gelem<R>::G* g) {
-  typedef typename gelem<R>::G G;
-  typedef TileThreads<NT> TT;
+// Addresses of the lane's stores: in load order the wpos positions of the
+// element's bits, in destination order the lpos positions.
+template <typename R>
+struct PutMap {
+  uint64_t a0, hb[4];
+};
+template <typename R>
+__device__ __forceinline__ PutMap<R> put_map(const TileRef<R>& T) {
   constexpr int LB = gelem<R>::LB;
   const cptr<PassDescDev> P = T.P;
   const uint32_t m = P->m;
-  const LaneGeo lg = lane_geo<LB, NT>(m);
-  const gptr<G> gpsi = as_global(reinterpret_cast<G*>(T.psi));
   const cptr<uint32_t> pos = (P->flags & kPassStoreLaneOrder) ? P->wpos : P->lpos;
-  uint64_t a0 = T.base;
-  for (uint32_t j = 0; j < (uint32_t)TT::TB && LB + j < m; ++j)
-    if ((threadIdx.x >> j) & 1u) a0 |= 1ull << pos[LB + j];
-  uint64_t hb[TT::UB];
+  uint32_t tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  PutMap<R> p;
+  p.a0 = T.base;
 #pragma unroll
-  for (int b = 0; b < TT::UB; ++b) hb[b] = LB + TT::TB + b < (int)m ? 1ull << pos[LB + TT::TB + b] : 0ull;
+  for (uint32_t j = 0; j < 8; ++j) {
+    const uint64_t w = LB + j < m ? 1ull << pos[LB + j] : 0ull;
+    p.a0 |= ((tid >> j) & 1u) ? w : 0ull;
+  }
 #pragma unroll
-  for (int u = 0; u < TT::BATCH; ++u)
-    if ((uint32_t)u < lg.per && lg.on) {
-      uint64_t ad = a0;
+  for (int b = 0; b < 4; ++b) p.hb[b] = LB + 8 + b < (int)m ? 1ull << pos[LB + 8 + b] : 0ull;
+  return p;
+}
+template <typename R>
+__device__ __forceinline__ void put_one(const TileRef<R>& T, const PutMap<R>& p, uint32_t u, typename gelem<R>::G v) {
+  typedef typename gelem<R>::G G;
+  const gptr<G> gpsi = as_global(reinterpret_cast<G*>(T.psi));
+  uint64_t ad = p.a0;
 #pragma unroll
-      for (int b = 0; b < TT::UB; ++b)
-        if ((u >> b) & 1) ad |= hb[b];
-      stg<G>(gpsi + (ad >> LB), g[u]);
-    }
+  for (int b = 0; b < 4; ++b)
+    if ((u >> b) & 1) ad |= p.hb[b];
+  stg<G>(gpsi + (ad >> gelem<R>::LB), v);
 }
 
 // s_waitcnt with only the vector-memory counter (gfx9 encoding: expcnt and
@@ -839,6 +880,16 @@ __device__ __forceinline__ void wait_vm() {
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
+// Moves of a full tile (64 KiB: 16 elements per lane) are straight-line code,
+// those of a smaller tile a loop, and lanes without a group read group 0
+// instead of skipping their LDS reads: with a predicate per element every
+// read was a branch of its own, its result merged with an older register, and
+// the gathered elements were live (or spilled) through the whole loop.  With
+// the stage heads read in one burst and the store map's columns only where
+// there is a map: N = 26 passes of three QAOA levels 7.48 -> 6.37 ms
+// (complex128) and 4.05 -> 3.55 ms (complex64), ten layered levels 12.4 ->
+// 11.0 and 6.79 -> 5.96 ms; registers 248 -> 184 (complex128 with phase items).
+//
 // Persistent loop over tiles.  Per tile: the tile's loads land in LDS, the
 // stages run, the result is read back into registers, and after a barrier
 // the next tile's loads are issued before this tile's stores, so that the
@@ -852,7 +903,7 @@ __device__ __forceinline__ void tile_loop(uint64_t total, const Src& src, typena
   uint64_t g = xcd_block();
   if (g >= total) return;
   tile_load_lds<R>(src(g), tile);
-  bool full_prev = false;  // the previous tile stored kBatch elements per lane
+  bool full_prev = false;  // the previous tile's kBatch stores per lane follow the loads
   while (true) {
     const uint64_t ng = g + gridDim.x;
     const TileRef<R> cur = src(g);
@@ -863,14 +914,36 @@ __device__ __forceinline__ void tile_loop(uint64_t total, const Src& src, typena
     else wait_vm<0>();
     lds_barrier();
     tile_stages<R, LP>(cur, tile, pre, npre);
-    G out[kBatch];
-    tile_gather<R>(cur, tile, out);
-    wait_lgkm0();  // this lane's LDS reads are done
-    lds_barrier();
-    if (ng < total) tile_load_lds<R>(src(ng), tile);
-    asm volatile("" ::: "memory");  // the loads stay ahead of the stores
-    tile_put<R>(cur, out);
-    full_prev = lane_geo<gelem<R>::LB>(cur.P->m).per == (uint32_t)kBatch;
+    const LaneGeo lg = lane_geo<gelem<R>::LB>(cur.P->m);
+    full_prev = lg.full;
+    if (lg.full) {
+      G out[kBatch];
+      const GatherMap<R> gm = gather_map<R>(cur.P);
+      if (gm.lane_order) {
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) out[u] = gather_one<R>(gm, tile, u);
+      } else {
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) out[u] = gather_one<R>(gm, tile, u);
+      }
+      wait_lgkm0();  // this lane's LDS reads are done
+      lds_barrier();
+      if (ng < total) tile_load_lds<R>(src(ng), tile);
+      asm volatile("" ::: "memory");  // the loads stay ahead of the stores
+      const PutMap<R> pm = put_map<R>(cur);
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) put_one<R>(cur, pm, u, out[u]);
+    } else {  // a small tile: element by element
+      const GatherMap<R> gm = gather_map<R>(cur.P);
+      const PutMap<R> pm = put_map<R>(cur);
+      if (lg.on) {
+#pragma unroll 1
+        for (uint32_t u = 0; u < lg.per; ++u) put_one<R>(cur, pm, u, gather_one<R>(gm, tile, u));
+      }
+      wait_lgkm0();
+      lds_barrier();
+      if (ng < total) tile_load_lds<R>(src(ng), tile);
+    }
     if (ng >= total) break;
     g = ng;
   }

@@ -128,6 +128,7 @@ constexpr int kPassFormBits = 3;  // bits of one register bit's PassForm in a fo
 inline constexpr uint32_t pass_form_of(uint32_t word, int r) { return (word >> (kPassFormBits * r)) & 7u; }
 
 struct alignas(16) PassStageDev {
+  // the head: what the kernel reads of every stage, in one go
   uint32_t q[kPassRegBitsMax];      // local bit of register bit r (r < rb)
   uint32_t qsort[kPassRegBitsMax];  // the same bits, ascending (group enumeration)
   uint32_t form;                    // PassForm of each register bit (kPassFormBits each, bit 0 lowest)
@@ -140,10 +141,11 @@ struct alignas(16) PassStageDev {
   uint32_t mat_base;                // the stage's first pool entry
   uint32_t rows;                    // row descriptors: pool entry, from mat_base
   uint32_t row_count;               // <= kPassStageRowsMax
-  uint32_t colimg[kPassLocalMax];   // store map: image of local bit l (M e_l, a local mask)
   uint32_t pconst;                  // store map: constant XOR (local mask)
   uint32_t slot_mask;               // register bits whose 2x2 is not the identity
   uint32_t nsub;                    // earlier layers (<= kPassSubMax)
+  // read by the stages that need them
+  uint32_t colimg[kPassLocalMax];   // store map: image of local bit l (M e_l, a local mask)
   PassSubDev sub[kPassSubMax];
 };
 
