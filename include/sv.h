@@ -120,7 +120,10 @@ typedef struct {
                                reordering), restoring logical order at the end;
                                default 1                                      */
   int32_t fp32_mfma;        /* complex64 states: dense fused ops of >= 4
-                               qubits run as FP32 MFMA contractions; default 1 */
+                               qubits, and layers of tile passes, run on the
+                               matrix cores with FP32 accumulation (operands in
+                               FP32, or split exactly into three bf16 parts);
+                               default 1                                      */
   int32_t renorm_interval;  /* complex64 states: rescale to unit norm (FP64
                                norm) every R dense ops; 0 = never; default 0   */
   int32_t mode;             /* sv_mode; default SV_MODE_AUTO                   */
@@ -286,9 +289,10 @@ const char *sv_last_error(void);
  * A request loop keeps many states resident and advances all of them with one
  * step per pass (continuous batching): one kernel launch runs the next
  * in-cache tile pass of every active state, so requests admitted later join
- * the next launch and their work overlaps with older ones on the device;
- * a state whose next pass is a matrix, dense or sweep pass runs it as a
- * launch of its own in the same step. */
+ * the next launch and their work overlaps with older ones on the device
+ * (passes that need another variant of the kernel share a launch of theirs);
+ * a state whose next pass is a dense, sweep or complex128 matrix pass runs it
+ * as a launch of its own in the same step. */
 typedef struct sv_program sv_program;  /* the passes of one plan, in device memory */
 typedef struct sv_batcher sv_batcher;  /* launches one pass of many states at once        */
 
@@ -324,8 +328,9 @@ sv_status sv_program_destroy(sv_program *prog);
 sv_status sv_batcher_create(void *hip_stream, sv_batcher **out);
 
 /* One step: for every i < count, run pass pass_index[i] of programs[i] on
- * states[i] -- the tile and permutation passes of all items in one launch,
- * each matrix, dense or sweep pass in a launch of its own.  All states and programs must share one dtype; states[i] must
+ * states[i] -- the tile, permutation and complex64 matrix passes of all items
+ * in one launch per kernel variant they need, each complex128 matrix, dense or
+ * sweep pass in a launch of its own.  All states and programs must share one dtype; states[i] must
  * have programs[i]'s qubit count; a state may appear at most once.  Work is
  * enqueued on the batcher's stream: the caller orders it against other work
  * on the states (e.g. by creating the states on the same stream).  A state's

@@ -50,13 +50,13 @@ sv_status ensure_scratch(sv_state* s, size_t bytes) {
   return SV_OK;
 }
 
-sv_status upload(sv_state* s, const void* host, size_t bytes, void** dev) {
+sv_status upload(sv_state* s, const void* host, size_t bytes, size_t dev_bytes, void** dev) {
   if (s->up_pending) {
     // the staging buffer is rewritten below: wait until the last copy read it
     SV_HIP_TRY(hipEventSynchronize(s->up_done));
     s->up_pending = false;
   }
-  if (bytes > s->up_bytes) {
+  if (dev_bytes > s->up_bytes) {
     if (s->up_dev) {
       SV_HIP_TRY(hipStreamSynchronize(s->stream));
       SV_HIP_TRY(hipFree(s->up_dev));
@@ -65,7 +65,7 @@ sv_status upload(sv_state* s, const void* host, size_t bytes, void** dev) {
       s->up_bytes = 0;
     }
     size_t cap = 1 << 16;
-    while (cap < bytes) cap <<= 1;
+    while (cap < dev_bytes) cap <<= 1;
     if (hipMalloc(&s->up_dev, cap) != hipSuccess) return fail(SV_ERR_NOMEM, "cannot allocate upload buffer");
     if (hipHostMalloc(&s->up_host, cap, hipHostMallocDefault) != hipSuccess) {
       (void)hipFree(s->up_dev);
@@ -259,7 +259,7 @@ sv_status sv_apply_gate(sv_state* s, const sv_gate* g) {
     }
   }
   void* dev = nullptr;
-  if (sv_status st = upload(s, host.data(), host.size(), &dev)) return st;
+  if (sv_status st = upload(s, host.data(), host.size(), host.size(), &dev)) return st;
   return run_op_sweep(s, op, dev);
 }
 

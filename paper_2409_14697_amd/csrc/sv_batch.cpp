@@ -65,13 +65,18 @@ sv_status pack_program(const sv_plan* p, sv_program* prog) {
   return SV_OK;
 }
 
-// One pass of one state as its own launch on `stream`: matrix, dense and
-// sweep passes (the batched kernel runs tile and permutation passes).
+// Passes the batched kernel runs: tile and permutation passes, and the matrix
+// passes of complex64 states.
+bool batched_kind(int kind, sv_dtype dt) {
+  return kind == PASS_TILE || kind == PASS_PERMUTE || (kind == PASS_MATRIX && dt == SV_C64);
+}
+
+// One pass of one state as its own launch on `stream`: the other kinds.
 sv_status run_single_pass(const sv_program* p, int pass, sv_state* s, hipStream_t stream) {
   unsigned char* pd = (unsigned char*)p->dev;
   const int kind = p->pass_kind[pass];
   if (kind == PASS_MATRIX) {
-    SV_LAUNCH(launch_matrix_pass(s->dt, p->pass_mx_k[pass], s->ptr, s->n, p->pass_m[pass],
+    SV_LAUNCH(launch_matrix_pass(p->pass_mx_k[pass], s->ptr, s->n, p->pass_m[pass],
                                  (const PassDescDev*)(pd + p->packed.off_desc), p->packed.desc_index[pass],
                                  p->pass_stages[pass], (const PassStageDev*)(pd + p->packed.off_stage),
                                  pd + p->packed.off_pool, stream),
@@ -103,7 +108,7 @@ sv_status sv_program_bytes(const sv_plan* p, size_t* bytes) {
   if (!p || !bytes) return fail(SV_ERR_ARG, "null argument");
   sv_program tmp;
   if (sv_status st = pack_program(p, &tmp)) return st;
-  *bytes = tmp.packed.host.size();
+  *bytes = tmp.packed.dev_bytes;
   return SV_OK;
 }
 
@@ -117,7 +122,7 @@ sv_status sv_program_create(const sv_plan* p, void* dev_buf, size_t buf_bytes, v
   prog->stream = (hipStream_t)stream;
   sv_status st = pack_program(p, prog);
   if (st == SV_OK) {
-    const size_t bytes = prog->packed.host.size();
+    const size_t bytes = prog->packed.dev_bytes;
     if (dev_buf) {
       if (buf_bytes < bytes) st = fail(SV_ERR_ARG, "program buffer of %zu bytes, %zu needed", buf_bytes, bytes);
       prog->dev = dev_buf;
@@ -136,6 +141,7 @@ sv_status sv_program_create(const sv_plan* p, void* dev_buf, size_t buf_bytes, v
                                      prog->stream) != hipSuccess ||
                       hipEventRecord(prog->uploaded, prog->stream) != hipSuccess))
     st = fail(SV_ERR_DEVICE, "program upload failed");
+  if (st == SV_OK) st = build_fragments(prog->packed, (unsigned char*)prog->dev, prog->stream);
   if (st != SV_OK) {
     (void)hipStreamSynchronize(prog->stream);
     if (prog->owned) (void)hipFree(prog->dev);
@@ -192,12 +198,14 @@ sv_status sv_batcher_run(sv_batcher* b, int count, sv_state* const* states, cons
   if (!b) return fail(SV_ERR_ARG, "null batcher");
   if (count <= 0) return count == 0 ? SV_OK : fail(SV_ERR_ARG, "negative count");
   if (!states || !programs || !pass_index) return fail(SV_ERR_ARG, "null array");
-  std::vector<BatchItemDev> items;
-  items.reserve((size_t)count);
+  // items of one launch: those whose passes need the same kernel variant
+  struct Group {
+    std::vector<BatchItemDev> items;
+    uint64_t tiles = 0;
+    int max_m = 0;
+    bool ladders = false;
+  } groups[3];
   std::vector<int> single;  // items whose pass runs as a launch of its own
-  uint64_t tiles = 0;
-  int max_m = 0;
-  bool ladders = false;
   sv_dtype dt = SV_C128;
   for (int i = 0; i < count; ++i) {
     const sv_state* s = states[i];
@@ -211,30 +219,34 @@ sv_status sv_batcher_run(sv_batcher* b, int count, sv_state* const* states, cons
     for (int j = 0; j < i; ++j)
       if (states[j] == s) return fail(SV_ERR_ARG, "state %d appears twice in one batch", i);
     const int kind = p->pass_kind[pass_index[i]];
-    if (kind != PASS_TILE && kind != PASS_PERMUTE) {
+    if (!batched_kind(kind, dt)) {
       single.push_back(i);
       continue;
     }
     const int m = p->pass_m[pass_index[i]];
-    items.emplace_back();
-    BatchItemDev& it = items.back();
+    Group& gr = groups[(int)p->packed.pass_mx[pass_index[i]]];
+    gr.items.emplace_back();
+    BatchItemDev& it = gr.items.back();
     unsigned char* pd = (unsigned char*)p->dev;
     it.psi = s->ptr;
     it.passes = (const PassDescDev*)(pd + p->packed.off_desc);
     it.stages = (const PassStageDev*)(pd + p->packed.off_stage);
     it.items = (const PassItemDev*)(pd + p->packed.off_items);
     it.mats = pd + p->packed.off_pool;
-    it.tile_begin = tiles;
+    it.frags = pd + p->packed.off_frags;
+    it.tile_begin = gr.tiles;
     it.n = s->n;
     it.pass = p->packed.desc_index[pass_index[i]];
-    tiles += 1ull << (s->n - m);
-    max_m = std::max(max_m, m);
-    ladders = ladders || p->packed.pass_lp[pass_index[i]];
+    gr.tiles += 1ull << (s->n - m);
+    gr.max_m = std::max(gr.max_m, m);
+    gr.ladders = gr.ladders || p->packed.pass_lp[pass_index[i]];
   }
   for (int i : single)
     if (sv_status st = run_single_pass(programs[i], pass_index[i], states[i], b->stream)) return st;
-  if (items.empty()) return SV_OK;
-  const size_t bytes = items.size() * sizeof(BatchItemDev);
+  size_t n_items = 0;
+  for (const Group& gr : groups) n_items += gr.items.size();
+  if (!n_items) return SV_OK;
+  const size_t bytes = n_items * sizeof(BatchItemDev);
   const int k = b->next;
   b->next = (b->next + 1) % sv_batcher::kSlots;
   if (b->used[k]) SV_HIP_TRY(hipEventSynchronize(b->done[k]));  // slot's last launch has read it
@@ -258,10 +270,18 @@ sv_status sv_batcher_run(sv_batcher* b, int count, sv_state* const* states, cons
     }
     b->cap[k] = cap;
   }
-  std::memcpy(b->host[k], items.data(), bytes);
+  BatchItemDev* at = (BatchItemDev*)b->host[k];
+  for (const Group& gr : groups) at = std::copy(gr.items.begin(), gr.items.end(), at);
   SV_HIP_TRY(hipMemcpyAsync(b->dev[k], b->host[k], bytes, hipMemcpyHostToDevice, b->stream));
-  SV_LAUNCH(launch_pass_batch(dt, (const BatchItemDev*)b->dev[k], (int)items.size(), tiles, max_m, ladders, b->stream),
-            b->stream);
+  const BatchItemDev* dev = (const BatchItemDev*)b->dev[k];
+  for (int v = 0; v < 3; ++v) {
+    const Group& gr = groups[v];
+    if (gr.items.empty()) continue;
+    SV_LAUNCH(launch_pass_batch(dt, dev, (int)gr.items.size(), gr.tiles, gr.max_m, gr.ladders, (PassMatrix)v,
+                                b->stream),
+              b->stream);
+    dev += gr.items.size();
+  }
   SV_HIP_TRY(hipEventRecord(b->done[k], b->stream));
   b->used[k] = true;
   return SV_OK;

@@ -177,8 +177,9 @@ sv_status ensure_scratch(sv_state* s, size_t bytes);
 sv_status probs_args(int n, const int32_t* qubits, int m, const double* out_dev, int* qs);
 // Copy `bytes` from host memory to the state's upload buffer (stream-ordered);
 // returns the device address.  The previous upload's device contents stay
-// valid for work enqueued before this call.
-sv_status upload(sv_state* s, const void* host, size_t bytes, void** dev);
+// valid for work enqueued before this call.  dev_bytes (>= bytes): device
+// memory behind that address.
+sv_status upload(sv_state* s, const void* host, size_t bytes, size_t dev_bytes, void** dev);
 // Run one op as a full-state sweep (sweep kernels for nq <= 2, dense kernel
 // for nq >= 3 with the matrix at m_dev in the state's precision; mfma selects
 // the FP32 MFMA kernel for complex64 states and nq >= 4).
@@ -202,7 +203,8 @@ sv_status plan_tile_passes(const std::vector<Op>& ops, int n, sv_dtype dt, const
 // Matrix passes over a fused op list (logical = physical qubits): runs of
 // ops whose qubits, with the pinned low bits, fit one tile become one pass
 // of matrix-core stages; ops that do not pay off grouped run as sweeps.
-void plan_matrix_passes(const std::vector<Op>& fused, int n, sv_dtype dt, const sv_opts& o, sv_plan* p);
+// Returns the plan's cost in full-state sweeps; p null: the cost alone.
+double plan_matrix_passes(const std::vector<Op>& fused, int n, sv_dtype dt, const sv_opts& o, sv_plan* p);
 // Cost of one op run as its own sweep, in full read+write sweeps of the state.
 double op_sweep_cost(const Op& op, sv_dtype dt, bool mfma);
 // Tile size defaults.
@@ -218,8 +220,19 @@ struct PackedPlan {
   std::vector<size_t> dense_off;   // per pass: offset of its dense matrix (PASS_DENSE)
   std::vector<int> desc_index;     // per pass: descriptor index (PASS_TILE / PASS_PERMUTE / PASS_MATRIX) or -1
   std::vector<char> pass_lp;       // per pass: holds fixed-point phase items
+  std::vector<PassMatrix> pass_mx;  // per pass: where its register parts run
   size_t off_desc = 0, off_stage = 0, off_items = 0, off_pool = 0;
-  int n_desc = 0, max_m = 0;
+  size_t off_list = 0;             // stages with matrix fragments (launch_stage_frags)
+  size_t off_frags = 0;            // their fragments: device only, behind the image
+  size_t dev_bytes = 0;            // device memory of the image and the fragments
+  int n_desc = 0, max_m = 0, n_mx = 0;
 };
 sv_status pack_plan(const sv_plan* p, PackedPlan* out);
+// The register parts of a tile pass's stages (4x4, layers, register factors)
+// run as matrix products on the matrix cores.
+bool pass_on_matrix_cores(const std::vector<StageHost>& stages, sv_dtype dt, const sv_opts& o);
+// The stage has a register part beyond factors of the register index.
+bool stage_has_layers(const StageHost& sh);
+// Enqueue the build of an uploaded image's matrix fragments.
+sv_status build_fragments(const PackedPlan& pk, unsigned char* dev, hipStream_t s);
 }  // namespace sv

@@ -136,7 +136,7 @@ struct Stage {
   __device__ __forceinline__ uint32_t NAME() const { return h.w[offsetof(PassStageDev, NAME) / 4]; }
   SV_HEAD(form) SV_HEAD(flags) SV_HEAD(slots) SV_HEAD(u2) SV_HEAD(dr) SV_HEAD(item_first) SV_HEAD(item_count)
   SV_HEAD(px_first) SV_HEAD(px_count) SV_HEAD(mat_base) SV_HEAD(rows) SV_HEAD(row_count) SV_HEAD(pconst)
-  SV_HEAD(slot_mask) SV_HEAD(nsub)
+  SV_HEAD(slot_mask) SV_HEAD(nsub) SV_HEAD(mx)
 #undef SV_HEAD
   __device__ __forceinline__ uint32_t q(int b) const { return h.w[b]; }
   __device__ __forceinline__ uint32_t qsort(int b) const { return h.w[offsetof(PassStageDev, qsort) / 4 + b]; }
@@ -246,6 +246,264 @@ __device__ __forceinline__ void layer(cplx<R>* v, cptr<cplx<R>> M, uint32_t form
   slot<2>(v, M, forms);
   slot<3>(v, M, forms);
   if constexpr (Regs<R>::RB > 4) slot<4>(v, M, forms);
+}
+
+// ---- FP32 products on the bf16 matrix cores --------------------------------
+// The FP32 matrix instructions run at 1/16 of the bf16 rate (64 against 1024
+// flops per cycle and SIMD).  An FP32 value is exactly the sum of three bf16
+// values, h + m + l (the top 8 bits, the next 8 rounded to nearest, the
+// rest), each with the full FP32 exponent range, and products of bf16 values
+// are exact in the FP32 accumulator; of the nine part products of u x the
+// six of relative size >= 2^-17 are summed (smallest first), the dropped
+// ones are below 2^-25 |u x|, less than the rounding of one FP32 product.
+// Error against FP64 for Haar 32 x 32 blocks on Gaussian columns: 5.1e-8
+// relative, against 1.55e-7 for the three real FP32 products of Gauss's
+// complex multiplication (measured; the accumulator rounds once per sixteen
+// products instead of once per two, and Yi = P3 - P1 - P2 cancels).  Four
+// real products are formed (P1 = Ur Xr, P2 = Ui Xi, Yi = Ur Xi + Ui Xr).
+// Infinite and NaN amplitudes leave their whole group not finite, as any
+// complex product with them does.
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// The parts of (x, y), x in the low halves.  (v_dot2_f32_bf16 would form a
+// residual without unpacking, 7 instructions per pair against 11, but it does
+// not run beside a matrix instruction: 27 ns per MFMA with four of them
+// interleaved against 17 ns with any of the instructions used here.)
+__device__ __forceinline__ void split_bf16(float x, float y, uint32_t* h, uint32_t* m, uint32_t* l) {
+  const uint32_t xb = __builtin_bit_cast(uint32_t, x), yb = __builtin_bit_cast(uint32_t, y);
+  *h = __builtin_amdgcn_perm(yb, xb, 0x07060302u);  // truncated: a finite value stays finite
+  x -= __builtin_bit_cast(float, xb & 0xffff0000u);
+  y -= __builtin_bit_cast(float, yb & 0xffff0000u);
+  const uint32_t mm = __builtin_bit_cast(uint32_t, __builtin_convertvector(flt2{x, y}, bf16x2));
+  x -= __builtin_bit_cast(float, mm << 16);
+  y -= __builtin_bit_cast(float, mm & 0xffff0000u);
+  *m = mm;
+  *l = __builtin_bit_cast(uint32_t, __builtin_convertvector(flt2{x, y}, bf16x2));
+}
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+__device__ __forceinline__ f32x16 mma_bf16(u32x4 a, u32x4 b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0,
+                                                 0);
+}
+
+// Matrix fragments of a stage: one 16-byte entry (eight columns of a row) per
+// lane for part p, component c (0 real, 1 imaginary) and k-step ks.
+// v_mfma_f32_32x32x16_bf16: lane l holds A[l % 32][8 (l / 32) + j] and
+// B[8 (l / 32) + j][l % 32], j = 0..7 (two per register); accumulator
+// register r of lane l is C[8 (r / 4) + 4 (l / 32) + r % 4][l % 32].
+constexpr uint32_t frag_at(int p, int c, int ks) { return (uint32_t)(((p * 2 + c) * 2 + ks) * 64); }
+static_assert(frag_at(3, 0, 0) * 16 == kStageFragBytes, "fragment size");
+
+// One k-step of a column block: the operand fragments of its 32 columns
+// (members 16 ks + 8 (l / 32) + j, which a lane holds in x[j]).
+struct MxOperand {
+  u32x4 re[3], im[3];  // part
+};
+__device__ __forceinline__ MxOperand mx_split(const flt2* x) {
+  MxOperand b;
+#pragma unroll
+  for (int d = 0; d < 4; ++d) {
+    const flt2 x0 = x[2 * d], x1 = x[2 * d + 1];
+    uint32_t p[3];
+    split_bf16(x0.x, x1.x, &p[0], &p[1], &p[2]);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) b.re[k][d] = p[k];
+    split_bf16(x0.y, x1.y, &p[0], &p[1], &p[2]);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) b.im[k][d] = p[k];
+  }
+  return b;
+}
+struct MxProducts {
+  f32x16 rr = {}, ii = {}, im = {};  // Ur Xr, Ui Xi, Ur Xi + Ui Xr
+};
+// The part products of one k-step for NB column blocks (each A fragment is
+// read once for all of them).
+template <int NB>
+__device__ __forceinline__ void mx_products(const MxOperand* const* b, gptr<const u32x4> fr, int ks, MxProducts* const* p) {
+  constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+  for (int t = 0; t < 6; ++t) {
+    const u32x4 ar = fr[frag_at(pa[t], 0, 0) + 64 * ks], ai = fr[frag_at(pa[t], 1, 0) + 64 * ks];
+#pragma unroll
+    for (int c = 0; c < NB; ++c) {
+      p[c]->rr = mma_bf16(ar, b[c]->re[pb[t]], p[c]->rr);
+      p[c]->im = mma_bf16(ar, b[c]->im[pb[t]], p[c]->im);
+      p[c]->ii = mma_bf16(ai, b[c]->im[pb[t]], p[c]->ii);
+      p[c]->im = mma_bf16(ai, b[c]->re[pb[t]], p[c]->im);
+    }
+  }
+}
+
+// Exchange the upper half of the wave's lanes of a with the lower half of b.
+__device__ __forceinline__ void swap_halves(uint32_t& a, uint32_t& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  a = r[0];
+  b = r[1];
+}
+__device__ __forceinline__ void swap_halves(float& a, float& b) {
+  uint32_t x = __builtin_bit_cast(uint32_t, a), y = __builtin_bit_cast(uint32_t, b);
+  swap_halves(x, y);
+  a = __builtin_bit_cast(float, x);
+  b = __builtin_bit_cast(float, y);
+}
+
+// v <- U v for the 32 register amplitudes of every lane (all 64 lanes run
+// it).  A lane holds one column; the instruction wants 32 columns, each
+// spread over two lanes: exchanging the halves of the wave turns the 64
+// columns into two column blocks and the results back into columns, with
+// one lane exchange per pair of registers and no LDS traffic.
+__device__ __forceinline__ void mx_apply(cplx<float>* v, gptr<const u32x4> frags) {
+  const gptr<const u32x4> fr = frags + (threadIdx.x & 63u);
+  f32x16 p1[2], p2[2], p3[2];
+#pragma unroll
+  for (int cb = 0; cb < 2; ++cb) p1[cb] = p2[cb] = p3[cb] = f32x16{};
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) {
+    u32x4 br[2][3], bi[2][3];  // column block, part
+#pragma unroll
+    for (int d = 0; d < 4; ++d)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {  // members 16 ks + 8 h + 2 d, + 1
+        const cplx<float> x0 = v[16 * ks + 8 * h + 2 * d], x1 = v[16 * ks + 8 * h + 2 * d + 1];
+        uint32_t p[3];
+        split_bf16(x0.re, x1.re, &p[0], &p[1], &p[2]);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) br[h][k][d] = p[k];
+        split_bf16(x0.im, x1.im, &p[0], &p[1], &p[2]);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) bi[h][k][d] = p[k];
+      }
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+#pragma unroll
+      for (int d = 0; d < 4; ++d) {
+        uint32_t a = br[0][k][d], b = br[1][k][d];
+        swap_halves(a, b);
+        br[0][k][d] = a;
+        br[1][k][d] = b;
+        a = bi[0][k][d];
+        b = bi[1][k][d];
+        swap_halves(a, b);
+        bi[0][k][d] = a;
+        bi[1][k][d] = b;
+      }
+    constexpr int pa[6] = {2, 0, 1, 1, 0, 0}, pb[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+    for (int t = 0; t < 6; ++t) {
+      const u32x4 ar = fr[frag_at(pa[t], 0, ks)], ai = fr[frag_at(pa[t], 1, ks)];
+#pragma unroll
+      for (int cb = 0; cb < 2; ++cb) {
+        p1[cb] = mma_bf16(ar, br[cb][pb[t]], p1[cb]);
+        p3[cb] = mma_bf16(ar, bi[cb][pb[t]], p3[cb]);
+        p2[cb] = mma_bf16(ai, bi[cb][pb[t]], p2[cb]);
+        p3[cb] = mma_bf16(ai, br[cb][pb[t]], p3[cb]);
+      }
+    }
+    if (ks == 0) {  // the next k-step's splitting runs beside this one's products
+#pragma unroll
+      for (int q = 0; q < 48; ++q) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+      }
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int row = 8 * (r / 4) + r % 4;
+    float a = p1[0][r] - p2[0][r], b = p1[1][r] - p2[1][r];
+    swap_halves(a, b);
+    v[row].re = a;
+    v[row + 4].re = b;
+    a = p3[0][r];
+    b = p3[1][r];
+    swap_halves(a, b);
+    v[row].im = a;
+    v[row + 4].im = b;
+  }
+}
+
+// The three bf16 parts of an FP64 matrix entry, in the low halves.
+__device__ __forceinline__ uint32_t bf16_bits(float x) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(flt2{x, 0.f}, bf16x2)) & 0xffffu;
+}
+__device__ __forceinline__ void split_entry(double x, uint32_t* p) {
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    p[k] = bf16_bits((float)x);
+    x -= (double)__builtin_bit_cast(float, p[k] << 16);
+  }
+}
+
+// Build the matrix fragments of the listed stages, one block per stage: the
+// register part (4x4, layers, register factors) applied to the columns of
+// the identity in FP64, or the matrix of a matrix-pass stage.  Runs once per
+// upload of a program; a few microseconds, latency-bound.
+__global__ __launch_bounds__(kBlock) void k_stage_frags(const PassStageDev* __restrict__ stages,
+                                                        const uint32_t* __restrict__ list,
+                                                        const cplx<float>* __restrict__ mats, uint32_t* __restrict__ frags) {
+  constexpr int D = 32, NG = kBlock / D;
+  __shared__ cplx<double> U[D][D + 1];
+  const uint32_t e = list[blockIdx.x];
+  const cptr<PassStageDev> sp = as_const(stages) + (e & ~kFragMatrixStage);
+  const PassStageDev S = cload(sp);
+  const uint32_t c = threadIdx.x % D, g = threadIdx.x / D;
+  auto entry = [&](uint32_t i) { return cplx<double>{(double)mats[i].re, (double)mats[i].im}; };
+  if (e & kFragMatrixStage) {
+    for (uint32_t r = g; r < (uint32_t)D; r += NG) U[r][c] = entry(S.u2 + r * D + c);
+  } else {
+    for (uint32_t r = g; r < (uint32_t)D; r += NG) U[r][c] = cplx<double>{r == c ? 1.0 : 0.0, 0.0};
+    __syncthreads();
+    if (S.flags & PSF_U2) {
+      static_assert(NG * 4 == D, "one quad of rows per thread");
+      cplx<double> x[4], y[4];
+      for (int i = 0; i < 4; ++i) x[i] = U[4 * g + i][c];
+      for (int o = 0; o < 4; ++o) {
+        y[o] = cmul(entry(S.u2 + 4 * o), x[0]);
+        for (int i = 1; i < 4; ++i) y[o] = cfma(y[o], entry(S.u2 + 4 * o + i), x[i]);
+      }
+      for (int o = 0; o < 4; ++o) U[4 * g + o][c] = y[o];
+      __syncthreads();
+    }
+    for (uint32_t li = 0; li <= S.nsub; ++li) {
+      const bool last = li == S.nsub;
+      const cptr<PassSubDev> subs = (cptr<PassSubDev>)((cptr<uint32_t>)sp + offsetof(PassStageDev, sub) / 4);
+      const PassSubDev L = last ? PassSubDev{S.form, S.slot_mask, S.slots, (S.flags & PSF_DR) ? S.dr : kPassNoTable}
+                                : cload(subs + li);
+      for (int b = 0; b < 5; ++b) {
+        if (pass_form_of(L.form, b) == PFORM_NONE) continue;
+        const cplx<double> m0 = entry(L.slots + 4 * b), m1 = entry(L.slots + 4 * b + 1), m2 = entry(L.slots + 4 * b + 2),
+                           m3 = entry(L.slots + 4 * b + 3);
+        for (uint32_t p = g; p < (uint32_t)D / 2; p += NG) {
+          const uint32_t r0 = ((p >> b) << (b + 1)) | (p & ((1u << b) - 1u)), r1 = r0 | (1u << b);
+          const cplx<double> x0 = U[r0][c], x1 = U[r1][c];
+          U[r0][c] = cfma(cmul(m0, x0), m1, x1);
+          U[r1][c] = cfma(cmul(m2, x0), m3, x1);
+        }
+        __syncthreads();
+      }
+      if (L.dr != kPassNoTable) {
+        for (uint32_t r = g; r < (uint32_t)D; r += NG) U[r][c] = cmul(entry(L.dr + r), U[r][c]);
+        __syncthreads();
+      }
+    }
+  }
+  __syncthreads();
+  uint32_t* out = frags + (size_t)blockIdx.x * (kStageFragBytes / 4);
+  for (uint32_t f = threadIdx.x; f < 512; f += kBlock) {  // k-step, lane, register of the fragment
+    const uint32_t ks = f / 256, l = (f / 4) % 64, d = f % 4;
+    const cplx<double> a = U[l % 32][16 * ks + 8 * (l / 32) + 2 * d], b = U[l % 32][16 * ks + 8 * (l / 32) + 2 * d + 1];
+    uint32_t x[3], y[3];
+    split_entry(a.re, x);
+    split_entry(b.re, y);
+    for (int p = 0; p < 3; ++p) out[(frag_at(p, 0, 0) + ks * 64 + l) * 4 + d] = x[p] | (y[p] << 16);
+    split_entry(a.im, x);
+    split_entry(b.im, y);
+    for (int p = 0; p < 3; ++p) out[(frag_at(p, 1, 0) + ks * 64 + l) * 4 + d] = x[p] | (y[p] << 16);
+  }
 }
 
 // Angle words of the phase ladder: fixed-point turns, summed modulo one turn.
@@ -404,14 +662,15 @@ __device__ __forceinline__ cplx<R> pick(cptr<cplx<R>> T, uint32_t var, int n) {
   return x;
 }
 
-// The diagonal part with lane items: per lane a factor G on all amplitudes
+// The diagonal part with lane items (folded: without the register factors):
+// per lane a factor G on all amplitudes
 // and, per register bit a, factors f0[a] / f1[a] on the amplitudes whose bit
 // a is 0 / 1; amplitude r is multiplied by G * prod_a f_{r_a}[a] * dr[r].
 template <typename R, bool LP>
 __device__ __forceinline__ void lane_diag(const Stage& S, cptr<PassItemDev> items, cptr<cplx<R>> mats,
                                           uint32_t xg, uint64_t base, const typename lp_word<R>::W* ts,
                                           const typename lp_word<R>::W* pre, uint32_t npre, uint32_t* kfix,
-                                          cplx<R>* v) {
+                                          bool folded, cplx<R>* v) {
   typedef typename lp_word<R>::W W;
   constexpr int RB = Regs<R>::RB, NR = Regs<R>::NR, HALF = NR / 2;
   const cplx<R> one = {R(1), R(0)};
@@ -468,6 +727,14 @@ __device__ __forceinline__ void lane_diag(const Stage& S, cptr<PassItemDev> item
 #pragma unroll
       for (int k = 0; k < (1 << a); ++k) H[k | (1 << a)] = cmul(H[k], f1[a]);
   }
+  if (folded) {  // the register factors are part of the stage's matrix
+#pragma unroll
+    for (int r = 0; r < HALF; ++r) {
+      v[r] = cmul(cmul(H[r], f0[RB - 1]), v[r]);
+      v[r + HALF] = cmul(cmul(H[r], f1[RB - 1]), v[r + HALF]);
+    }
+    return;
+  }
   const cptr<cplx<R>> D = mats + S.dr();
 #pragma unroll
   for (int r = 0; r < HALF; ++r) {
@@ -503,19 +770,21 @@ struct TileRef {
   cptr<PassStageDev> stages;
   cptr<PassItemDev> items;
   cptr<cplx<R>> mats;
+  const void* frags;  // matrix fragments of the program's stages (complex64)
   uint64_t base;
 };
 
 template <typename R>
 __device__ __forceinline__ TileRef<R> tile_ref(typename dev_elem<R>::E* psi, int n, cptr<PassDescDev> P,
                                                cptr<PassStageDev> stages, cptr<PassItemDev> items,
-                                               cptr<cplx<R>> mats, uint64_t tile_id) {
+                                               cptr<cplx<R>> mats, const void* frags, uint64_t tile_id) {
   TileRef<R> r;
   r.psi = uniform_ptr(psi);
   r.P = uniform_ptr(P);
   r.stages = uniform_ptr(stages);
   r.items = uniform_ptr(items);
   r.mats = uniform_ptr(mats);
+  r.frags = uniform_ptr(frags);
   r.base = uniform64(deposit(tile_id, ((1ull << n) - 1ull) & ~r.P->lmask));
   return r;
 }
@@ -643,7 +912,150 @@ __device__ __forceinline__ uint32_t pre_fill(cptr<PassDescDev> P, cptr<PassStage
   return k;
 }
 
-template <typename R, bool LP>
+// Offsets of one stage of a matrix pass: a lane's columns and members in the
+// swizzled tile.
+struct MxGeo {
+  uint32_t sb[5];      // member bits
+  uint32_t in0, out0;  // the lane's first column block: operand and result rows
+  uint32_t next;       // from a wave's first column block to its second
+};
+// Rows a lane reads (member 16 (i / 8) + 8 (l / 32) + i % 8) and writes
+// (member 8 (r / 4) + 4 (l / 32) + r % 4), lane part left out.
+__device__ __forceinline__ uint32_t mx_in(const MxGeo& g, int i) {
+  return ((i & 1) ? g.sb[0] : 0u) ^ ((i & 2) ? g.sb[1] : 0u) ^ ((i & 4) ? g.sb[2] : 0u) ^ ((i & 8) ? g.sb[4] : 0u);
+}
+__device__ __forceinline__ uint32_t mx_out(const MxGeo& g, int r) {
+  return ((r & 1) ? g.sb[0] : 0u) ^ ((r & 2) ? g.sb[1] : 0u) ^ ((r & 4) ? g.sb[3] : 0u) ^ ((r & 8) ? g.sb[4] : 0u);
+}
+// PAIRS: member bit 0 is local bit 0, members 2 i and 2 i + 1 share a 16-byte
+// slot (else local bit 0 is a lane bit: both ways the accesses spread over
+// all banks).
+template <bool PAIRS>
+__device__ __forceinline__ void mx_read(const MxGeo& g, const flt2* tile, uint32_t at, flt2* x) {
+#pragma unroll
+  for (int i = 0; i < 16; i += 2) {
+    if constexpr (PAIRS) {
+      const flt4 v = *reinterpret_cast<const flt4*>(tile + (at ^ mx_in(g, i)));
+      x[i] = flt2{v.x, v.y};
+      x[i + 1] = flt2{v.z, v.w};
+    } else {
+      x[i] = tile[at ^ mx_in(g, i)];
+      x[i + 1] = tile[at ^ mx_in(g, i + 1)];
+    }
+  }
+}
+template <bool PAIRS>
+__device__ __forceinline__ void mx_write(const MxGeo& g, const MxProducts& p, uint32_t at, flt2* tile) {
+#pragma unroll
+  for (int r = 0; r < 16; r += 2) {
+    const flt2 y0 = {p.rr[r] - p.ii[r], p.im[r]}, y1 = {p.rr[r + 1] - p.ii[r + 1], p.im[r + 1]};
+    if constexpr (PAIRS) {
+      *reinterpret_cast<flt4*>(tile + (at ^ mx_out(g, r))) = flt4{y0.x, y0.y, y1.x, y1.y};
+    } else {
+      tile[at ^ mx_out(g, r)] = y0;
+      tile[at ^ mx_out(g, r + 1)] = y1;
+    }
+  }
+}
+
+// One stage on a wave's two column blocks.  A matrix instruction (32 cycles)
+// leaves room for six VALU instructions of the two waves of a SIMD (measured),
+// so the second k-step is split beside the first one's products.  Both blocks
+// share each A fragment: reading them once per block instead costs more than
+// finishing one block early gains (N = 28, 6 stages: 2.31 against 2.20 ms).
+template <bool PAIRS>
+__device__ __forceinline__ void mx_stage_two(const MxGeo& g, gptr<const u32x4> fr, flt2* tile) {
+  flt2 x0[16], x1[16];
+  mx_read<PAIRS>(g, tile, g.in0, x0);
+  mx_read<PAIRS>(g, tile, g.in0 ^ g.next, x1);
+  MxProducts p0, p1;
+  const MxOperand b0 = mx_split(x0), b1 = mx_split(x1);
+  const MxOperand* const b[2] = {&b0, &b1};
+  MxProducts* const p[2] = {&p0, &p1};
+  __builtin_amdgcn_sched_barrier(0);
+  mx_products<2>(b, fr, 0, p);
+  const MxOperand c0 = mx_split(x0 + 8), c1 = mx_split(x1 + 8);
+#pragma unroll
+  for (int i = 0; i < 48; ++i) {
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
+    __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);  // VALU
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  const MxOperand* const c[2] = {&c0, &c1};
+  mx_products<2>(c, fr, 1, p);
+  __builtin_amdgcn_sched_barrier(0);
+  mx_write<PAIRS>(g, p0, g.out0, tile);
+  mx_write<PAIRS>(g, p1, g.out0 ^ g.next, tile);
+}
+template <bool PAIRS>
+__device__ __forceinline__ void mx_stage_one(const MxGeo& g, gptr<const u32x4> fr, flt2* tile) {
+  flt2 x[16];
+  mx_read<PAIRS>(g, tile, g.in0, x);
+  MxProducts p0;
+  MxProducts* const p[1] = {&p0};
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) {
+    const MxOperand b0 = mx_split(x + 8 * ks);
+    const MxOperand* const b[1] = {&b0};
+    mx_products<1>(b, fr, ks, p);
+  }
+  mx_write<PAIRS>(g, p0, g.out0, tile);
+}
+
+// The stages of a complex64 matrix pass.  Column bit j of a stage is local
+// bit colimg[j]: lane bits first, then wave bits; wave w owns the column
+// blocks w and w + 4 and overwrites them in place, so stages without
+// kMatrixStageSync (which keep every element with its wave) need no barrier.
+__device__ __forceinline__ void matrix_stages(const TileRef<float>& T, flt2* tile) {
+  constexpr int LB = 1, NW = kBlock / 64;
+  const cptr<PassDescDev> P = T.P;
+  const uint32_t m = P->m, ns = P->stage_count;
+  const uint32_t l = threadIdx.x & 63u;
+  const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t cblocks = 1u << (m - 10u);
+  for (uint32_t si = 0; si < ns; ++si) {
+    const cptr<PassStageDev> S = T.stages + (P->stage_first + si);
+    if (si > 0) {
+      if (S->flags & kMatrixStageSync) {
+        lds_sync();
+      } else {  // the stage reads only what this wave wrote
+        wait_lgkm0();
+        asm volatile("" ::: "memory");
+      }
+    }
+    const gptr<const u32x4> fr = as_global(reinterpret_cast<const u32x4*>(T.frags)) + (size_t)S->mx * (kStageFragBytes / 16) + l;
+    MxGeo g;
+#pragma unroll
+    for (int b = 0; b < 5; ++b) g.sb[b] = swz<LB>(1u << S->q[b]);
+    uint32_t col = 0;  // the lane's column bits
+#pragma unroll
+    for (int j = 0; j < 5; ++j) col ^= ((l >> j) & 1u) ? swz<LB>(1u << S->colimg[j]) : 0u;
+    uint32_t wc[3];  // column block bits
+#pragma unroll
+    for (int j = 0; j < 3; ++j) wc[j] = 5u + j < m - 5u ? swz<LB>(1u << S->colimg[5 + j]) : 0u;
+    col ^= ((w & 1u) ? wc[0] : 0u) ^ ((w & 2u) ? wc[1] : 0u);
+    g.in0 = col ^ (l >= 32u ? g.sb[3] : 0u);
+    g.out0 = col ^ (l >= 32u ? g.sb[2] : 0u);
+    g.next = wc[2];
+    const bool pairs = S->q[0] == 0;
+    if (cblocks == 2 * NW) {
+      if (pairs) mx_stage_two<true>(g, fr, tile);
+      else mx_stage_two<false>(g, fr, tile);
+    } else if (w < cblocks) {  // a small tile: one column block per wave
+      if (pairs) mx_stage_one<true>(g, fr, tile);
+      else mx_stage_one<false>(g, fr, tile);
+    }
+  }
+  lds_sync();
+}
+
+// Kernel variants (each carries only the code its passes need).  LP: the
+// pass holds fixed-point phase items.  MX_NONE: the register parts of its
+// stages run on the VALU; MX_TILE: on the matrix cores; MX_ONLY: a matrix
+// pass, whose stages are matrices and nothing else.
+enum { MX_NONE = 0, MX_TILE = 1, MX_ONLY = 2 };
+
+template <typename R, bool LP, int MX>
 __device__ __forceinline__ void tile_stages(const TileRef<R>& T, typename dev_elem<R>::E* tile,
                                             const typename lp_word<R>::W* pre, uint32_t npre) {
   typedef typename dev_elem<R>::E E;
@@ -712,24 +1124,32 @@ __device__ __forceinline__ void tile_stages(const TileRef<R>& T, typename dev_el
         const E e = tile[o];
         v[r] = cplx<R>{e.x, e.y};
       }
-      if (flags & PSF_U2) op_u2<R>(v, mats + S.u2());
-      // the earlier layers (2x2s, then register factors), then the last one;
-      // one copy of the layer code serves all of them
-      const cptr<PassSubDev> subs = (cptr<PassSubDev>)((cptr<uint32_t>)S.p + offsetof(PassStageDev, sub) / 4);
-      for (uint32_t li = 0; li <= S.nsub(); ++li) {
-        const bool last = li == S.nsub();
-        const PassSubDev L = last ? PassSubDev{S.form(), S.slot_mask(), S.slots(), kPassNoTable} : cload(subs + li);
-        if (L.form) layer<R>(v, mats + L.slots, L.form);
-        if (L.dr != kPassNoTable) {
-          const cptr<cplx<R>> D = mats + L.dr;
+      bool folded = false;  // the register factors are part of the stage's matrix
+      if constexpr (MX != MX_NONE) {
+        if (S.mx() != kPassNoTable) {
+          mx_apply(v, as_global(reinterpret_cast<const u32x4*>(T.frags)) + (size_t)S.mx() * (kStageFragBytes / 16));
+          folded = true;
+        }
+      } else {
+        if (flags & PSF_U2) op_u2<R>(v, mats + S.u2());
+        // the earlier layers (2x2s, then register factors), then the last one;
+        // one copy of the layer code serves all of them
+        const cptr<PassSubDev> subs = (cptr<PassSubDev>)((cptr<uint32_t>)S.p + offsetof(PassStageDev, sub) / 4);
+        for (uint32_t li = 0; li <= S.nsub(); ++li) {
+          const bool last = li == S.nsub();
+          const PassSubDev L = last ? PassSubDev{S.form(), S.slot_mask(), S.slots(), kPassNoTable} : cload(subs + li);
+          if (L.form) layer<R>(v, mats + L.slots, L.form);
+          if (L.dr != kPassNoTable) {
+            const cptr<cplx<R>> D = mats + L.dr;
 #pragma unroll
-          for (int r = 0; r < NR; ++r) v[r] = cmul(cget(D, r), v[r]);
+            for (int r = 0; r < NR; ++r) v[r] = cmul(cget(D, r), v[r]);
+          }
         }
       }
       if (flags & PSF_LANE) {
         uint32_t kf = kfix;
-        lane_diag<R, LP>(S, items, mats, xg, base, tsum, pre, npre, &kf, v);
-      } else if (flags & PSF_DR) {
+        lane_diag<R, LP>(S, items, mats, xg, base, tsum, pre, npre, &kf, folded, v);
+      } else if (!folded && (flags & PSF_DR)) {
         const cptr<cplx<R>> D = mats + S.dr();
 #pragma unroll
         for (int r = 0; r < NR; ++r) v[r] = cmul(cget(D, r), v[r]);
@@ -896,7 +1316,7 @@ __device__ __forceinline__ void wait_vm() {
 // wait for a tile's data never waits for the previous tile's stores (the
 // vector-memory counter retires in issue order).  The two blocks a CU holds
 // overlap one block's memory phase with the other's stages.
-template <typename R, bool LP, typename Src>
+template <typename R, bool LP, int MX, typename Src>
 __device__ __forceinline__ void tile_loop(uint64_t total, const Src& src, typename dev_elem<R>::E* tile,
                                           const typename lp_word<R>::W* pre, uint32_t npre) {
   typedef typename gelem<R>::G G;
@@ -913,7 +1333,8 @@ __device__ __forceinline__ void tile_loop(uint64_t total, const Src& src, typena
     if (full_prev) wait_vm<kBatch>();
     else wait_vm<0>();
     lds_barrier();
-    tile_stages<R, LP>(cur, tile, pre, npre);
+    if constexpr (MX == MX_ONLY) matrix_stages(cur, tile);
+    else tile_stages<R, LP, MX>(cur, tile, pre, npre);
     const LaneGeo lg = lane_geo<gelem<R>::LB>(cur.P->m);
     full_prev = lg.full;
     if (lg.full) {
@@ -957,22 +1378,22 @@ struct SingleSrc {
   cptr<PassStageDev> stages;
   cptr<PassItemDev> items;
   cptr<cplx<R>> mats;
+  const void* frags;
   __device__ __forceinline__ TileRef<R> operator()(uint64_t g) const {
-    return tile_ref<R>(psi, n, P, stages, items, mats, g);
+    return tile_ref<R>(psi, n, P, stages, items, mats, frags, g);
   }
 };
 
-template <typename R, bool LP>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_pass(typename dev_elem<R>::E* __restrict__ psi, int n,
-                                                 const PassDescDev* __restrict__ passes, int pi,
-                                                 const PassStageDev* __restrict__ stages,
-                                                 const PassItemDev* __restrict__ items,
-                                                 const cplx<R>* __restrict__ mats) {
+template <typename R, bool LP, int MX>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_pass(
+    typename dev_elem<R>::E* __restrict__ psi, int n, const PassDescDev* __restrict__ passes, int pi,
+    const PassStageDev* __restrict__ stages, const PassItemDev* __restrict__ items,
+    const cplx<R>* __restrict__ mats, const void* __restrict__ frags) {
   typedef typename dev_elem<R>::E E;
   extern __shared__ __align__(16) unsigned char smem[];
   E* tile = reinterpret_cast<E*>(smem);
   const cptr<PassDescDev> P = as_const(passes + pi);
-  const SingleSrc<R> src{psi, n, P, as_const(stages), as_const(items), as_const(mats)};
+  const SingleSrc<R> src{psi, n, P, as_const(stages), as_const(items), as_const(mats), frags};
   typedef typename lp_word<R>::W W;
   // lane parts of the fixed-point phase items, computed once for all tiles
   __shared__ W pre[LP ? pre_cap<R>::N * kBlock : 1];
@@ -981,7 +1402,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) 
     npre = pre_fill<R>(P, as_const(stages), as_const(items), as_const(mats), pre, pre_cap<R>::N);
     wait_lgkm0();  // the table is complete before the first tile's barrier
   }
-  tile_loop<R, LP>(1ull << (n - P->m), src, tile, pre, npre);
+  tile_loop<R, LP, MX>(1ull << (n - P->m), src, tile, pre, npre);
 }
 
 // Many states in one launch: work item i runs pass `pass` of its own program
@@ -1003,58 +1424,69 @@ struct BatchSrc {
     const cptr<BatchItemDev> it = items + lo;  // fields read one by one: scalar loads
     return tile_ref<R>((typename dev_elem<R>::E*)it->psi, it->n, as_const(it->passes + it->pass),
                        as_const(it->stages), as_const(it->items), as_const((const cplx<R>*)it->mats),
-                       g - it->tile_begin);
+                       it->frags, g - it->tile_begin);
   }
 };
 
-template <typename R, bool LP>
+template <typename R, bool LP, int MX>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_pass_batch(const BatchItemDev* __restrict__ items, int count,
                                                        uint64_t total_tiles) {
   typedef typename dev_elem<R>::E E;
   extern __shared__ __align__(16) unsigned char smem[];
   E* tile = reinterpret_cast<E*>(smem);
   const BatchSrc<R> src{as_const(items), count};
-  tile_loop<R, LP>(total_tiles, src, tile, nullptr, 0);
+  tile_loop<R, LP, MX>(total_tiles, src, tile, nullptr, 0);
 }
 
-template <typename R, bool LP>
-hipError_t run(void* psi, int n, int m, const PassDescDev* passes, int pass, const PassStageDev* stages,
-               const PassItemDev* items, const void* mats, hipStream_t s) {
+struct PassRun {
+  void* psi;
+  int n, m;
+  const PassDescDev* passes;
+  int pass;
+  const PassStageDev* stages;
+  const PassItemDev* items;
+  const void *mats, *frags;
+  hipStream_t s;
+};
+
+template <typename R, bool LP, int MX>
+hipError_t run(const PassRun& r) {
   typedef typename dev_elem<R>::E E;
-  const size_t lds = ((size_t)1 << m) * sizeof(E);
+  const size_t lds = ((size_t)1 << r.m) * sizeof(E);
   static KernelLaunchCache cache;
   uint64_t resident = 0;
-  hipError_t e = prepare_launch(cache, (const void*)k_pass<R, LP>, kBlock, lds, &resident);
+  hipError_t e = prepare_launch(cache, (const void*)k_pass<R, LP, MX>, kBlock, lds, &resident);
   if (e != hipSuccess) return e;
-  const uint64_t tiles = 1ull << (n - m);
+  const uint64_t tiles = 1ull << (r.n - r.m);
   const uint64_t blocks = tiles < resident ? tiles : resident;
-  hipLaunchKernelGGL((k_pass<R, LP>), dim3((unsigned)blocks), dim3(kBlock), lds, s, (E*)psi, n, passes, pass, stages,
-                     items, (const cplx<R>*)mats);
+  hipLaunchKernelGGL((k_pass<R, LP, MX>), dim3((unsigned)blocks), dim3(kBlock), lds, r.s, (E*)r.psi, r.n, r.passes,
+                     r.pass, r.stages, r.items, (const cplx<R>*)r.mats, r.frags);
   return hipGetLastError();
 }
 
-template <typename R, bool LP>
+template <typename R, bool LP, int MX>
 hipError_t run_batch(const BatchItemDev* items, int count, uint64_t total_tiles, int max_m, hipStream_t s) {
   typedef typename dev_elem<R>::E E;
   const size_t lds = ((size_t)1 << max_m) * sizeof(E);
   static KernelLaunchCache cache;
   uint64_t resident = 0;
-  hipError_t e = prepare_launch(cache, (const void*)k_pass_batch<R, LP>, kBlock, lds, &resident);
+  hipError_t e = prepare_launch(cache, (const void*)k_pass_batch<R, LP, MX>, kBlock, lds, &resident);
   if (e != hipSuccess) return e;
   if (total_tiles == 0) return hipSuccess;
   const uint64_t blocks = total_tiles < resident ? total_tiles : resident;
-  hipLaunchKernelGGL((k_pass_batch<R, LP>), dim3((unsigned)blocks), dim3(kBlock), lds, s, items, count, total_tiles);
+  hipLaunchKernelGGL((k_pass_batch<R, LP, MX>), dim3((unsigned)blocks), dim3(kBlock), lds, s, items, count, total_tiles);
   return hipGetLastError();
 }
 
 // ---------------------------------------------------------------- matrix passes
-// A matrix pass runs dense fused ops (general gate fusion, Sec. II-B) inside
+// A complex128 matrix pass (complex64 ones run as tile passes whose stages
+// are matrices) runs dense fused ops (general gate fusion, Sec. II-B) inside
 // the tiles of one pass (in-cache operation, Sec. II-B / III-B), on the
 // matrix cores.  Stage s views the tile as a 2^K x 2^(m-K) matrix X: rows
 // ("members") are the K local bits of the stage (member bit b = local bit
 // q[b]), columns the other local bits in the stage's column order (lane
-// bits, wave bits, the rest).  It computes Y = U X with three real products
-// (Gauss's complex multiplication):
+// bits, wave bits, the rest).  It computes Y = U X with three real FP64
+// products (Gauss's complex multiplication):
 //   P1 = Ur Xr,  P2 = Ui Xi,  P3 = (Ur + Ui)(Xr + Xi),  Yr = P1 - P2,
 //   Yi = P3 - P1 - P2.
 // Every wave owns whole column blocks (those whose wave bits spell its
@@ -1065,42 +1497,24 @@ hipError_t run_batch(const BatchItemDev* items, int count, uint64_t total_tiles,
 // stages run and are written to LDS once the current tile has been read
 // back; a tile's stores go out after the next tile's first stage.  A block
 // (eight waves, two per SIMD) is the only one on its CU.
-typedef float mx_f32x16 __attribute__((ext_vector_type(16)));
 typedef double mx_f64x4 __attribute__((ext_vector_type(4)));
 
-template <typename R>
-struct mx_shape;
-template <>
-struct mx_shape<float> {
-  // v_mfma_f32_32x32x2f32: lane l holds A[l % 32][l / 32] and B[l / 32][l % 32];
-  // accumulator register r of lane l is C[8 (r / 4) + 4 (l / 32) + r % 4][l % 32]
-  static constexpr int BM = 32, BN = 32, BK = 2, NACC = 16;
-  typedef mx_f32x16 acc_t;
-  static __device__ __forceinline__ acc_t mma(float a, float b, acc_t c) {
-    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
-  }
-  static constexpr uint32_t out_u(int r) { return 8 * (r / 4) + r % 4; }  // row: register part
-  static __device__ __forceinline__ uint32_t out_l(uint32_t l) { return 4 * (l / 32); }  // row: lane part
-};
-template <>
-struct mx_shape<double> {
-  // v_mfma_f64_16x16x4f64: lane l holds A[l % 16][l / 16] and B[l / 16][l % 16];
-  // accumulator register r of lane l is C[l / 16 + 4 r][l % 16]
+// v_mfma_f64_16x16x4f64: lane l holds A[l % 16][l / 16] and B[l / 16][l % 16];
+// accumulator register r of lane l is C[l / 16 + 4 r][l % 16]
+struct mx_shape {
   static constexpr int BM = 16, BN = 16, BK = 4, NACC = 4;
   typedef mx_f64x4 acc_t;
   static __device__ __forceinline__ acc_t mma(double a, double b, acc_t c) {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
   }
-  static constexpr uint32_t out_u(int r) { return 4 * r; }
-  static __device__ __forceinline__ uint32_t out_l(uint32_t l) { return l / 16; }
 };
 
-template <typename R, int K>
+template <int K>
 struct mx_plan {
   static constexpr int D = 1 << K;
-  static constexpr int RBK = D / mx_shape<R>::BM;  // row blocks
-  static constexpr int KS = D / mx_shape<R>::BK;   // k-steps
-  static constexpr int AF = RBK * KS * 64;         // A-fragment entries of one stage
+  static constexpr int RBK = D / mx_shape::BM;  // row blocks
+  static constexpr int KS = D / mx_shape::BK;   // k-steps
+  static constexpr int AF = RBK * KS * 64;      // A-fragment entries of one stage
   static_assert(RBK >= 1, "a stage fills at least one row block");
   static_assert(AF == D * D, "one A-fragment entry per matrix entry (matrix_pass_max_stages)");
 };
@@ -1124,65 +1538,68 @@ constexpr int kMxThreads = 512;
 // the tile; every offset is an XOR of swizzled bit offsets, so offsets of
 // disjoint bit sets combine by XOR), filled once per block:
 //   [kMxBoff + ks]           member BK ks (operand reads, uniform part)
-//   [kMxOoff + rb NACC + r]  member BM rb + out_u(r) (results, uniform part)
+//   [kMxOoff + rb NACC + r]  member BM rb + 4 r (results, uniform part)
 //   [kMxCol + cb]            column BN cb
-//   [kMxLane + 2 l (+ 1)]    lane l: column l % BN with member l / BN (with
-//                            the lane part out_l(l) of the result member)
+//   [kMxLane + l]            lane l: column l % BN with member l / BN
 constexpr int kMxBoff = 0, kMxOoff = 16, kMxCol = 48, kMxLane = 64, kMxTab = 192;
 static_assert(kMxTab * 4 == kMatrixStageTable, "table size shared with the planner");
 
-template <typename R, int K>
-__device__ __forceinline__ void mx_table(cptr<uint32_t> sd, uint32_t m, uint32_t* tab) {
-  typedef mx_shape<R> MS;
-  typedef mx_plan<R, K> MP;
-  constexpr int LB = gelem<R>::LB;
-  constexpr uint32_t EB = sizeof(typename dev_elem<R>::E);
-  constexpr int LBN = MS::BN == 32 ? 5 : 4;  // lane bits of a column block
-  const cptr<uint32_t> q = sd + offsetof(PassStageDev, q) / 4;
-  const cptr<uint32_t> col = sd + offsetof(PassStageDev, colimg) / 4;  // column bit j: local bit col[j]
-  uint32_t sm[K];
-#pragma unroll
-  for (int b = 0; b < K; ++b) sm[b] = swz<LB>(1u << q[b]) * EB;
-  const uint32_t nc = m - K;  // column bits
+// Fill the tables of stages 0..ns-1, one entry of one stage per thread and
+// step (the stages' reads are in flight together).
+template <int K>
+__device__ __forceinline__ void mx_tables(const PassStageDev* __restrict__ st, uint32_t ns, uint32_t m, uint32_t* tab) {
+  typedef mx_shape MS;
+  typedef mx_plan<K> MP;
+  constexpr uint32_t EB = sizeof(dbl2);
+  constexpr int LBN = 4;     // lane bits of a column block
+  constexpr int NC = 12 - K;  // column bits, at most
+  const uint32_t nc = m - K;
   const uint32_t cblocks = (1u << nc) / MS::BN;
-  // offset of the column bits `v` taken from column bit `first` on
-  auto cols = [&](uint32_t v, uint32_t first, uint32_t nbits) {
-    uint32_t o = 0;
-    for (uint32_t j = 0; j < nbits; ++j)
-      if ((v >> j) & 1u) o ^= swz<LB>(1u << col[first + j]) * EB;
-    return o;
-  };
-  for (uint32_t t = threadIdx.x; t < (uint32_t)kMxTab; t += kMxThreads) {
-    uint32_t v = 0;
-    if (t < (uint32_t)kMxBoff + MP::KS) {
-      v = mx_member<K>(MS::BK * (t - kMxBoff), sm);
-    } else if (t >= (uint32_t)kMxOoff && t < (uint32_t)kMxOoff + MP::RBK * MS::NACC) {
+  for (uint32_t e = threadIdx.x; e < ns * (uint32_t)kMxTab; e += kMxThreads) {
+    const PassStageDev* S = st + e / kMxTab;
+    const uint32_t t = e % kMxTab;
+    uint32_t sm[K], sc[NC];  // swizzled offsets of the member and column bits
+#pragma unroll
+    for (int b = 0; b < K; ++b) sm[b] = swz<0>(1u << S->q[b]) * EB;
+#pragma unroll
+    for (int j = 0; j < NC; ++j) sc[j] = (uint32_t)j < nc ? swz<0>(1u << S->colimg[j]) * EB : 0u;
+    uint32_t mem = 0, col = 0;
+    bool used = true;
+    if (t < (uint32_t)kMxOoff) {
+      used = t < (uint32_t)MP::KS;
+      mem = MS::BK * (t - kMxBoff);
+    } else if (t < (uint32_t)kMxCol) {
       const uint32_t i = t - kMxOoff;
-      v = mx_member<K>(MS::BM * (i / MS::NACC) + MS::out_u((int)(i % MS::NACC)), sm);
-    } else if (t >= (uint32_t)kMxCol && t < (uint32_t)kMxCol + cblocks) {
-      v = cols(t - kMxCol, LBN, nc - LBN);
-    } else if (t >= (uint32_t)kMxLane) {
-      const uint32_t l = (t - kMxLane) / 2;
-      v = cols(l % MS::BN, 0, LBN) ^ mx_member<K>(((t - kMxLane) & 1u) ? MS::out_l(l) : l / MS::BN, sm);
+      used = i < (uint32_t)(MP::RBK * MS::NACC);
+      mem = MS::BM * (i / MS::NACC) + 4 * (i % MS::NACC);
+    } else if (t < (uint32_t)kMxLane) {
+      used = t - kMxCol < cblocks;
+      col = (t - kMxCol) << LBN;
+    } else {
+      const uint32_t l = t - kMxLane;
+      used = l < 64u;
+      col = l % MS::BN;
+      mem = (l / MS::BN) % 4u;
     }
-    tab[t] = v;
+    uint32_t v = mx_member<K>(mem, sm);
+#pragma unroll
+    for (int j = 0; j < NC; ++j) v ^= ((col >> j) & 1u) ? sc[j] : 0u;
+    tab[e] = used ? v : 0u;
   }
 }
 
 // One stage on the tile in LDS (no barrier inside).  tab: the stage's
 // address table; am: its A fragments, entry (rb KS + ks) 64 + l =
 // U[BM rb + l % BM][BK ks + l / BM].  Each wave owns whole column blocks.
-template <typename R, int K>
-__device__ __forceinline__ void mx_stage(typename dev_elem<R>::E* tile, const uint32_t* tab, const cplx<R>* am,
-                                         uint32_t m) {
-  typedef mx_shape<R> MS;
-  typedef mx_plan<R, K> MP;
-  typedef typename dev_elem<R>::E E;
+template <int K>
+__device__ __forceinline__ void mx_stage(dbl2* tile, const uint32_t* tab, const cplx<double>* am, uint32_t m) {
+  typedef mx_shape MS;
+  typedef mx_plan<K> MP;
   unsigned char* tb = reinterpret_cast<unsigned char*>(tile);
   const uint32_t l = threadIdx.x & 63u;
   const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t cblocks = (1u << (m - K)) / MS::BN;
-  const uint32_t lb = tab[kMxLane + 2 * l], lo = tab[kMxLane + 2 * l + 1];
+  const uint32_t lb = tab[kMxLane + l];
   // the result offsets are read with the operands' and held in registers:
   // read next to their stores, each would cost a wait on the LDS queue
   constexpr int NO = MP::RBK * MS::NACC;
@@ -1192,18 +1609,17 @@ __device__ __forceinline__ void mx_stage(typename dev_elem<R>::E* tile, const ui
 #pragma unroll
   for (int j = 0; j < NO; ++j) asm volatile("" : "+v"(oo[j]));
   for (uint32_t cb = w; cb < cblocks; cb += kMxThreads / 64) {
-    const uint32_t cu = tab[kMxCol + cb];
-    const uint32_t bb = lb ^ cu, bo = lo ^ cu;
-    typename MS::acc_t p1[MP::RBK], p2[MP::RBK], p3[MP::RBK];
+    const uint32_t bb = lb ^ tab[kMxCol + cb];
+    MS::acc_t p1[MP::RBK], p2[MP::RBK], p3[MP::RBK];
 #pragma unroll
-    for (int rb = 0; rb < MP::RBK; ++rb) p1[rb] = p2[rb] = p3[rb] = typename MS::acc_t{};
+    for (int rb = 0; rb < MP::RBK; ++rb) p1[rb] = p2[rb] = p3[rb] = MS::acc_t{};
 #pragma unroll
     for (int ks = 0; ks < MP::KS; ++ks) {
-      const E x = *reinterpret_cast<const E*>(tb + (bb ^ tab[kMxBoff + ks]));
-      const R xs = x.x + x.y;
+      const dbl2 x = *reinterpret_cast<const dbl2*>(tb + (bb ^ tab[kMxBoff + ks]));
+      const double xs = x.x + x.y;
 #pragma unroll
       for (int rb = 0; rb < MP::RBK; ++rb) {
-        const cplx<R> a = am[(rb * MP::KS + ks) * 64 + l];
+        const cplx<double> a = am[(rb * MP::KS + ks) * 64 + l];
         p1[rb] = MS::mma(a.re, x.x, p1[rb]);
         p2[rb] = MS::mma(a.im, x.y, p2[rb]);
         p3[rb] = MS::mma(a.re + a.im, xs, p3[rb]);
@@ -1214,10 +1630,10 @@ __device__ __forceinline__ void mx_stage(typename dev_elem<R>::E* tile, const ui
     for (int rb = 0; rb < MP::RBK; ++rb)
 #pragma unroll
       for (int r = 0; r < MS::NACC; ++r) {
-        E y;
+        dbl2 y;
         y.x = p1[rb][r] - p2[rb][r];
         y.y = p3[rb][r] - p1[rb][r] - p2[rb][r];
-        *reinterpret_cast<E*>(tb + (bo ^ oo[rb * MS::NACC + r])) = y;
+        *reinterpret_cast<dbl2*>(tb + (bb ^ oo[rb * MS::NACC + r])) = y;
       }
   }
 }
@@ -1286,18 +1702,18 @@ __device__ __forceinline__ void tile_slots(typename gelem<R>::G* v, typename dev
     }
 }
 
-template <typename R, int K>
+template <int K>
 __global__ __launch_bounds__(kMxThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_mpass(
-    typename dev_elem<R>::E* __restrict__ psi, int n, const PassDescDev* __restrict__ passes, int pi,
-    const PassStageDev* __restrict__ stages, const cplx<R>* __restrict__ mats) {
-  typedef typename dev_elem<R>::E E;
-  typedef typename gelem<R>::G G;
-  typedef mx_shape<R> MS;
-  typedef mx_plan<R, K> MP;
+    dbl2* __restrict__ psi, int n, const PassDescDev* __restrict__ passes, int pi,
+    const PassStageDev* __restrict__ stages, const cplx<double>* __restrict__ mats) {
+  typedef double R;
+  typedef gelem<R>::G G;
+  typedef mx_shape MS;
+  typedef mx_plan<K> MP;
   extern __shared__ __align__(16) unsigned char smem[];
   const cptr<PassDescDev> P = as_const(passes + pi);
   const uint32_t m = P->m, ns = P->stage_count;
-  E* tile = reinterpret_cast<E*>(smem);
+  dbl2* tile = reinterpret_cast<dbl2*>(smem);
   cplx<R>* am = reinterpret_cast<cplx<R>*>(tile + (1u << m));
   uint32_t* tab = reinterpret_cast<uint32_t*>(am + ns * MP::AF);
   const cptr<PassStageDev> st = as_const(stages) + P->stage_first;
@@ -1310,9 +1726,9 @@ __global__ __launch_bounds__(kMxThreads) __attribute__((amdgpu_waves_per_eu(2, 2
       const uint32_t row = MS::BM * rb + l % MS::BM, col = MS::BK * ks + l / MS::BM;
       if (f < (uint32_t)MP::AF) am[s * MP::AF + f] = mats[at + row * MP::D + col];
     }
-    mx_table<R, K>((cptr<uint32_t>)(st + s), m, tab + s * kMxTab);
   }
-  const SingleSrc<R> src{psi, n, P, as_const(stages), as_const((const PassItemDev*)nullptr), as_const(mats)};
+  mx_tables<K>(stages + P->stage_first, ns, m, tab);
+  const SingleSrc<R> src{psi, n, P, as_const(stages), as_const((const PassItemDev*)nullptr), as_const(mats), nullptr};
   const MoveGeo<NT> mg = move_geo<R, NT>(P);
   const uint64_t total = 1ull << (n - m);
   uint64_t g = xcd_block();
@@ -1341,7 +1757,7 @@ __global__ __launch_bounds__(kMxThreads) __attribute__((amdgpu_waves_per_eu(2, 2
           asm volatile("" ::: "memory");
         }
       }
-      mx_stage<R, K>(tile, tab + s * kMxTab, am + s * MP::AF, m);
+      mx_stage<K>(tile, tab + s * kMxTab, am + s * MP::AF, m);
       if (s == 0 && prev < total) tile_move<R, NT, true>(src(prev), mg, out);
     }
     lds_sync();  // every wave's results are in LDS
@@ -1356,54 +1772,60 @@ __global__ __launch_bounds__(kMxThreads) __attribute__((amdgpu_waves_per_eu(2, 2
   tile_move<R, NT, true>(src(prev), mg, out);
 }
 
-template <typename R, int K>
+template <int K>
 hipError_t run_mpass(void* psi, int n, int m, const PassDescDev* passes, int pass, int n_stages,
                      const PassStageDev* stages, const void* mats, hipStream_t s) {
-  typedef typename dev_elem<R>::E E;
-  const size_t lds = ((size_t)1 << m) * sizeof(E) +
-                     (size_t)n_stages * (mx_plan<R, K>::AF * sizeof(cplx<R>) + kMxTab * sizeof(uint32_t));
+  const size_t lds = ((size_t)1 << m) * sizeof(dbl2) +
+                     (size_t)n_stages * (mx_plan<K>::AF * sizeof(cplx<double>) + kMxTab * sizeof(uint32_t));
   if (lds > (size_t)kMatrixPassLds) return hipErrorInvalidValue;
   static KernelLaunchCache cache;
   uint64_t resident = 0;
-  hipError_t e = prepare_launch(cache, (const void*)k_mpass<R, K>, kMxThreads, lds, &resident);
+  hipError_t e = prepare_launch(cache, (const void*)k_mpass<K>, kMxThreads, lds, &resident);
   if (e != hipSuccess) return e;
   const uint64_t tiles = 1ull << (n - m);
   const uint64_t blocks = tiles < resident ? tiles : resident;
-  hipLaunchKernelGGL((k_mpass<R, K>), dim3((unsigned)blocks), dim3(kMxThreads), lds, s, (E*)psi, n, passes, pass,
-                     stages, (const cplx<R>*)mats);
+  hipLaunchKernelGGL((k_mpass<K>), dim3((unsigned)blocks), dim3(kMxThreads), lds, s, (dbl2*)psi, n, passes, pass,
+                     stages, (const cplx<double>*)mats);
   return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_matrix_pass(sv_dtype dt, int k, void* psi, int n, int m, const PassDescDev* passes, int pass,
-                              int n_stages, const PassStageDev* stages, const void* mats, hipStream_t s) {
-  if (dt == SV_C64) {
-    if (k != 5) return hipErrorInvalidValue;
-    return run_mpass<float, 5>(psi, n, m, passes, pass, n_stages, stages, mats, s);
-  }
-  if (k == 4) return run_mpass<double, 4>(psi, n, m, passes, pass, n_stages, stages, mats, s);
-  if (k == 5) return run_mpass<double, 5>(psi, n, m, passes, pass, n_stages, stages, mats, s);
+hipError_t launch_matrix_pass(int k, void* psi, int n, int m, const PassDescDev* passes, int pass, int n_stages,
+                              const PassStageDev* stages, const void* mats, hipStream_t s) {
+  if (k == 4) return run_mpass<4>(psi, n, m, passes, pass, n_stages, stages, mats, s);
+  if (k == 5) return run_mpass<5>(psi, n, m, passes, pass, n_stages, stages, mats, s);
   return hipErrorInvalidValue;
 }
 
+hipError_t launch_stage_frags(const PassStageDev* stages, const uint32_t* list, int count, const void* pool,
+                              void* frags, hipStream_t s) {
+  hipLaunchKernelGGL(k_stage_frags, dim3((unsigned)count), dim3(kBlock), 0, s, stages, list, (const cplx<float>*)pool,
+                     (uint32_t*)frags);
+  return hipGetLastError();
+}
+
 hipError_t launch_pass(sv_dtype dt, void* psi, int n, int m, const PassDescDev* passes, int pass,
-                       const PassStageDev* stages, const PassItemDev* items, const void* mats, bool ladders,
-                       hipStream_t s) {
-  if (dt == SV_C128)
-    return ladders ? run<double, true>(psi, n, m, passes, pass, stages, items, mats, s)
-                   : run<double, false>(psi, n, m, passes, pass, stages, items, mats, s);
-  return ladders ? run<float, true>(psi, n, m, passes, pass, stages, items, mats, s)
-                 : run<float, false>(psi, n, m, passes, pass, stages, items, mats, s);
+                       const PassStageDev* stages, const PassItemDev* items, const void* mats, const void* frags,
+                       bool ladders, PassMatrix mx, hipStream_t s) {
+  const PassRun r{psi, n, m, passes, pass, stages, items, mats, frags, s};
+  if (dt == SV_C128) return ladders ? run<double, true, MX_NONE>(r) : run<double, false, MX_NONE>(r);
+  if (mx == kPassMatrixOnly) return run<float, false, MX_ONLY>(r);
+  if (mx == kPassMatrixTile) return ladders ? run<float, true, MX_TILE>(r) : run<float, false, MX_TILE>(r);
+  return ladders ? run<float, true, MX_NONE>(r) : run<float, false, MX_NONE>(r);
 }
 
 hipError_t launch_pass_batch(sv_dtype dt, const BatchItemDev* items, int count, uint64_t total_tiles, int max_m,
-                             bool ladders, hipStream_t s) {
+                             bool ladders, PassMatrix mx, hipStream_t s) {
   if (dt == SV_C128)
-    return ladders ? run_batch<double, true>(items, count, total_tiles, max_m, s)
-                   : run_batch<double, false>(items, count, total_tiles, max_m, s);
-  return ladders ? run_batch<float, true>(items, count, total_tiles, max_m, s)
-                 : run_batch<float, false>(items, count, total_tiles, max_m, s);
+    return ladders ? run_batch<double, true, MX_NONE>(items, count, total_tiles, max_m, s)
+                   : run_batch<double, false, MX_NONE>(items, count, total_tiles, max_m, s);
+  if (mx == kPassMatrixOnly) return run_batch<float, false, MX_ONLY>(items, count, total_tiles, max_m, s);
+  if (mx == kPassMatrixTile)
+    return ladders ? run_batch<float, true, MX_TILE>(items, count, total_tiles, max_m, s)
+                   : run_batch<float, false, MX_TILE>(items, count, total_tiles, max_m, s);
+  return ladders ? run_batch<float, true, MX_NONE>(items, count, total_tiles, max_m, s)
+                 : run_batch<float, false, MX_NONE>(items, count, total_tiles, max_m, s);
 }
 
 }  // namespace sv

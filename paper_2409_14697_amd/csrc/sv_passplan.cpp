@@ -819,6 +819,18 @@ std::vector<StageHost> build_stages(const std::vector<Op>& ops, const int* loc, 
   return out;
 }
 
+// VALU instructions per amplitude of a stage's register part.
+double register_ops(const StageHost& sh, int rb) {
+  double ops = 0.0;
+  for (int r = 0; r < rb; ++r) ops += form_ops(pass_form_of(sh.form, r));
+  if (sh.flags & PSF_U2) ops += 16.0;
+  for (uint32_t k = 0; k < sh.nsub; ++k) {
+    for (int r = 0; r < rb; ++r) ops += form_ops(pass_form_of(sh.sub[k].form, r));
+    if (sh.sub[k].dr != kPassNoTable) ops += 4.0;
+  }
+  return ops;
+}
+
 // Cost of a stage in VALU instructions per amplitude (the 2x2 part, the
 // diagonal part) plus its LDS round trip.
 double stage_ops(const StageHost& sh, sv_dtype dt) {
@@ -922,6 +934,28 @@ std::vector<std::vector<int>> dest_cycles(const std::vector<int>& d) {
 }
 
 }  // namespace
+
+bool stage_has_layers(const StageHost& sh) { return sh.form != PFORM_NONE || sh.nsub > 0 || (sh.flags & PSF_U2); }
+
+// A stage's matrix product costs the same whatever it holds (96 matrix
+// instructions per wave beside the splitting of its operands); the VALU form
+// costs its instructions per amplitude.  Measured: stages of 30-45 (QFT blocks
+// of five Hadamards with their phases) N = 28 6.8 ms on the matrix cores
+// against 8.2 ms; stages of about 18 (one layer of rotations) N = 26 7.3
+// against 6.4 ms the other way.
+constexpr double kMatrixStageOps = 24.0;
+
+bool pass_on_matrix_cores(const std::vector<StageHost>& stages, sv_dtype dt, const sv_opts& o) {
+  if (dt != SV_C64 || !o.fp32_mfma) return false;
+  double ops = 0.0;
+  int n = 0;
+  for (const StageHost& sh : stages)
+    if (stage_has_layers(sh)) {
+      ops += register_ops(sh, pass_reg_bits(dt));
+      ++n;
+    }
+  return n > 0 && ops >= kMatrixStageOps * n;
+}
 
 sv_status plan_tile_passes(const std::vector<Op>& ops, int n, sv_dtype dt, const sv_opts& o, sv_plan* p,
                            bool progress, int reserve) {

@@ -245,11 +245,24 @@ Op widened(const Op& o, const int* extra, int e) {
   return r;
 }
 
-// Cost of a matrix pass in full-state sweeps, measured on MI355X at N = 30
-// (both precisions): a fixed part (the tile traffic the stages do not hide)
-// plus 0.84 sweeps per stage of 32 members (the matrix cores at about 0.65
-// of their dense peak), half that for 16 members.
-double matrix_pass_cost(int k, int stages) { return 0.65 + 0.84 * stages * (double)(1 << k) / 32.0; }
+// Cost of a matrix pass in full-state sweeps, measured on MI355X (N = 28
+// complex64, N = 30 complex128): a fixed part (the tile traffic the stages do
+// not hide) plus 0.38 sweeps per stage (complex64: bf16 products of split
+// operands, 0.252 ms per stage against 0.46 ms of FP32 products) or 0.84 per
+// stage of 32 members (complex128: FP64 matrix cores at about 0.65 of their
+// peak), half that for 16 members.
+double matrix_pass_cost(sv_dtype dt, int k, int stages) {
+  if (dt == SV_C64) return 0.98 + 0.38 * stages;
+  return 0.65 + 0.84 * stages * (double)(1 << k) / 32.0;
+}
+
+// Bank class of local bit b in the kernels' LDS layout: the low bits of the
+// swizzled index of amplitude 2^b inside a 128-byte row (sv_pass.hip, swz;
+// complex64 rows hold 16 amplitudes, complex128 rows 8).
+uint32_t bank_class(sv_dtype dt, int b) {
+  const int lb = dt == SV_C64 ? 1 : 0;
+  return b < lb ? 1u : 1u << (lb + (b - lb) % 3);
+}
 
 // Column orders and barriers of a matrix pass's stages: runs of consecutive
 // stages share three wave bits that are a member of none of them (so each
@@ -281,23 +294,33 @@ void assign_matrix_columns(Pass& ps, sv_dtype dt) {
       }
     for (size_t si = s0; si < s1; ++si) {
       StageHost& sh = ps.stages[si];
-      const uint32_t rest = all & ~targets(sh) & ~wave;
-      int j = 0, taken = 0;
-      for (int b = 0; b < m && taken < lane_bits; ++b)
+      uint32_t rest = all & ~targets(sh) & ~wave;
+      int j = 0;
+      // lane bits: first those that select different LDS banks (complex64:
+      // lanes of one LDS cycle that differ in bits of the same bank class
+      // collide, 1.2e8 conflict cycles of a 6-stage pass at N = 28 against
+      // 2.6e8; complex128 is bound by its products, no change), then the
+      // lowest others
+      uint32_t span = 1u;  // bank classes the bits chosen so far reach (bit c: class c)
+      for (int b = 0; dt == SV_C64 && b < m && j < lane_bits; ++b) {
+        const uint32_t c = bank_class(dt, b);
+        if (!((rest >> b) & 1u) || ((span >> c) & 1u)) continue;
+        uint32_t more = span;
+        for (uint32_t x = 0; x < 16u; ++x)
+          if ((span >> x) & 1u) more |= 1u << (x ^ c);
+        span = more;
+        sh.colimg[j++] = (uint32_t)b;
+        rest &= ~(1u << b);
+      }
+      for (int b = 0; b < m && j < lane_bits; ++b)
         if ((rest >> b) & 1u) {
           sh.colimg[j++] = (uint32_t)b;
-          ++taken;
+          rest &= ~(1u << b);
         }
       for (int b = 0; b < m; ++b)
         if ((wave >> b) & 1u) sh.colimg[j++] = (uint32_t)b;
-      for (int b = 0, skip = lane_bits; b < m; ++b)
-        if ((rest >> b) & 1u) {
-          if (skip > 0) {
-            --skip;
-            continue;
-          }
-          sh.colimg[j++] = (uint32_t)b;
-        }
+      for (int b = 0; b < m; ++b)
+        if ((rest >> b) & 1u) sh.colimg[j++] = (uint32_t)b;
       sh.flags = (si == s0 && si > 0) ? kMatrixStageSync : 0u;
     }
     s0 = s1;
@@ -310,19 +333,23 @@ int matrix_width(sv_dtype dt, int k) { return dt == SV_C64 ? 5 : std::max(4, k);
 
 }  // namespace
 
-void plan_matrix_passes(const std::vector<Op>& fused, int n, sv_dtype dt, const sv_opts& o, sv_plan* p) {
+double plan_matrix_passes(const std::vector<Op>& fused, int n, sv_dtype dt, const sv_opts& o, sv_plan* p) {
+  double est_cost = 0.0;
   const bool mfma = dt == SV_C64 && o.fp32_mfma;
   const int m = std::min(n, dt == SV_C64 ? 13 : 12);  // 64 KiB tiles
   const int pin = std::min(default_pinned_bits(dt), m);
   // four column blocks of the instruction per stage (one per wave)
   const int min_cols = dt == SV_C64 ? 7 : 6;
-  p->ops.clear();
-  p->op_pass.clear();
-  p->passes.clear();
-  p->est_cost = 0.0;
+  if (p) {
+    p->ops.clear();
+    p->op_pass.clear();
+    p->passes.clear();
+  }
   std::vector<char> done(fused.size(), 0);
   size_t first = 0;
   auto emit_sweep = [&](const Op& op) {
+    est_cost += sweep_cost(op, dt, mfma);
+    if (!p) return;
     Pass ps;
     ps.kind = op.nq >= 3 ? PASS_DENSE : PASS_SWEEP;
     ps.first_op = (int)p->ops.size();
@@ -330,7 +357,6 @@ void plan_matrix_passes(const std::vector<Op>& fused, int n, sv_dtype dt, const 
     ps.phys = op;
     p->op_pass.push_back((int)p->passes.size());
     p->ops.push_back(op);
-    p->est_cost += sweep_cost(op, dt, mfma);
     p->passes.push_back(std::move(ps));
   };
   while (true) {
@@ -371,12 +397,15 @@ void plan_matrix_passes(const std::vector<Op>& fused, int n, sv_dtype dt, const 
     }
     double as_sweeps = 0.0;
     for (size_t j : members) as_sweeps += sweep_cost(fused[j], dt, mfma);
-    const double cost = members.empty() ? 0.0 : matrix_pass_cost(kw, (int)members.size());
+    const double cost = members.empty() ? 0.0 : matrix_pass_cost(dt, kw, (int)members.size());
     if (members.empty() || cost >= as_sweeps) {
       emit_sweep(fused[first]);
       done[first] = 1;
       continue;
     }
+    est_cost += cost;
+    for (size_t j : members) done[j] = 1;
+    if (!p) continue;
     // the tile: the group's qubits, the pinned bits, then the lowest others
     for (int b = 0; b < n && count < m; ++b)
       if (!in_l[b]) {
@@ -410,21 +439,34 @@ void plan_matrix_passes(const std::vector<Op>& fused, int n, sv_dtype dt, const 
       }
       const Op w = e ? widened(op, extra, e) : op;
       StageHost sh;
-      // member bit b is op qubit q[kw - 1 - b] (q[0] is the most significant)
-      for (int b = 0; b < kw; ++b) sh.q[b] = (uint32_t)loc[w.q[kw - 1 - b]];
+      // op qubit q[kw - 1 - b] is bit b of the matrix index (q[0] is the most
+      // significant); complex64: member bits are the local bits in ascending
+      // order, so that members on local bit 0, adjacent in LDS, are members
+      // 2 i, 2 i + 1
+      int order[8];  // member bit -> bit of the matrix index
+      for (int b = 0; b < kw; ++b) order[b] = b;
+      if (dt == SV_C64)
+        std::sort(order, order + kw, [&](int x, int y) { return loc[w.q[kw - 1 - x]] < loc[w.q[kw - 1 - y]]; });
+      for (int b = 0; b < kw; ++b) sh.q[b] = (uint32_t)loc[w.q[kw - 1 - order[b]]];
+      const int dim = 1 << kw;
+      std::vector<int> idx(dim, 0);  // matrix index of a member
+      for (int x = 0; x < dim; ++x)
+        for (int b = 0; b < kw; ++b) idx[x] |= ((x >> b) & 1) << order[b];
       sh.u2 = 0;
-      sh.mats = w.m;
+      sh.mats.resize(w.m.size());
+      for (int r = 0; r < dim; ++r)
+        for (int c = 0; c < dim; ++c) sh.mats[(size_t)r * dim + c] = w.m[(size_t)idx[r] * dim + idx[c]];
       sh.raw.assign(sh.mats.size(), 0);
       sh.n_ops = 1;
       ps.stages.push_back(std::move(sh));
       p->ops.push_back(op);
       p->op_pass.push_back(pass_id);
-      done[j] = 1;
     }
     assign_matrix_columns(ps, dt);
-    p->est_cost += matrix_pass_cost(kw, (int)members.size());
     p->passes.push_back(std::move(ps));
   }
+  if (p) p->est_cost = est_cost;
+  return est_cost;
 }
 
 sv_status build_plan(int n, sv_dtype dt, const sv_gate* g, size_t n_gates, const sv_opts& o, sv_plan* p) {
@@ -485,17 +527,17 @@ sv_status build_plan(int n, sv_dtype dt, const sv_gate* g, size_t n_gates, const
     std::vector<Op> fused = fuse_ops(raw, n, dt, o.max_fuse_qubits, mfma);
     double sweep_total = 0.0;
     for (const Op& op : fused) sweep_total += sweep_cost(op, dt, mfma);
-    sv_plan mq;
-    mq.n = n;
-    mq.dt = dt;
-    mq.opts = o;
-    plan_matrix_passes(fused, n, dt, o, &mq);
-    sv_plan* best = tp.est_cost <= mq.est_cost ? &tp : &mq;
-    if (best->est_cost <= sweep_total) {
-      p->ops = std::move(best->ops);
-      p->op_pass = std::move(best->op_pass);
-      p->passes = std::move(best->passes);
-      p->est_cost = best->est_cost;
+    // (the matrix plan's stages are built only if it is the cheapest)
+    const double matrix_total = plan_matrix_passes(fused, n, dt, o, nullptr);
+    if (tp.est_cost <= matrix_total && tp.est_cost <= sweep_total) {
+      p->ops = std::move(tp.ops);
+      p->op_pass = std::move(tp.op_pass);
+      p->passes = std::move(tp.passes);
+      p->est_cost = tp.est_cost;
+      return SV_OK;
+    }
+    if (matrix_total <= sweep_total) {
+      plan_matrix_passes(fused, n, dt, o, p);
       return SV_OK;
     }
     p->ops = std::move(fused);
@@ -542,7 +584,9 @@ sv_status pack_plan(const sv_plan* p, PackedPlan* out) {
   out->dense_off.assign(p->passes.size(), 0);
   out->desc_index.assign(p->passes.size(), -1);
   out->pass_lp.assign(p->passes.size(), 0);
+  out->pass_mx.assign(p->passes.size(), kPassMatrixNone);
   out->max_m = 0;
+  std::vector<uint32_t> mx_list;  // stages with matrix fragments
   std::vector<PassDescDev> descs;
   std::vector<PassStageDev> stages;
   std::vector<PassItemDev> items;
@@ -562,6 +606,8 @@ sv_status pack_plan(const sv_plan* p, PackedPlan* out) {
     if (ps.kind == PASS_MATRIX)  // the matrix-pass kernel stores where it loaded
       for (int j = 0; j < ps.n_local; ++j)
         if (ps.wpos[j] != ps.lpos[j]) return fail(SV_ERR_UNSUPPORTED, "internal: matrix pass with a write map");
+    if (f32 && ps.kind == PASS_MATRIX) out->pass_mx[i] = kPassMatrixOnly;
+    else if (pass_on_matrix_cores(ps.stages, p->dt, p->opts)) out->pass_mx[i] = kPassMatrixTile;
     for (const StageHost& sh : ps.stages) {
       PassStageDev sd{};
       // register bits of a tile stage, members of a matrix stage
@@ -594,6 +640,11 @@ sv_status pack_plan(const sv_plan* p, PackedPlan* out) {
         it.mat += mbase;
         items.push_back(it);
       }
+      sd.mx = kPassNoTable;
+      if (out->pass_mx[i] == kPassMatrixOnly || (out->pass_mx[i] == kPassMatrixTile && stage_has_layers(sh))) {
+        sd.mx = (uint32_t)mx_list.size();
+        mx_list.push_back((uint32_t)stages.size() | (ps.kind == PASS_MATRIX ? kFragMatrixStage : 0u));
+      }
       sd.px_first = (uint32_t)items.size();
       sd.px_count = (uint32_t)sh.px.size();
       items.insert(items.end(), sh.px.begin(), sh.px.end());
@@ -609,56 +660,15 @@ sv_status pack_plan(const sv_plan* p, PackedPlan* out) {
   out->n_desc = (int)descs.size();
   if (!descs.empty()) {
     out->off_desc = put(descs.data(), descs.size() * sizeof(PassDescDev));
+    out->off_list = put(mx_list.data(), mx_list.size() * sizeof(uint32_t));
     out->off_stage = put(stages.data(), stages.size() * sizeof(PassStageDev));
     out->off_items = put(items.data(), items.size() * sizeof(PassItemDev));
     out->off_pool = put_cd(pool.data(), pool.size(), pool_raw.data());
   }
   align();
-  return SV_OK;
-}
-
-sv_status execute_plan(sv_state* s, const sv_plan* p) {
-  PackedPlan pk;
-  if (sv_status st = pack_plan(p, &pk)) return st;
-  void* dev = nullptr;
-  if (!pk.host.empty()) {
-    sv_status st = upload(s, pk.host.data(), pk.host.size(), &dev);
-    if (st != SV_OK) return st;
-  }
-  unsigned char* db = (unsigned char*)dev;
-  // complex64 states: FP64 renormalisation after every `renorm` dense ops
-  const int renorm = s->dt == SV_C64 ? p->opts.renorm_interval : 0;
-  int since = 0;
-  for (size_t i = 0; i < p->passes.size(); ++i) {
-    const Pass& ps = p->passes[i];
-    if (ps.kind == PASS_SWEEP) {
-      sv_status st = run_op_sweep(s, ps.phys, nullptr);
-      if (st != SV_OK) return st;
-    } else if (ps.kind == PASS_DENSE) {
-      sv_status st = run_op_sweep(s, ps.phys, db + pk.dense_off[i], p->opts.fp32_mfma != 0);
-      if (st != SV_OK) return st;
-      if (renorm > 0 && ++since >= renorm) {
-        if (sv_status r = renormalize(s)) return r;
-        since = 0;
-      }
-    } else if (ps.kind == PASS_MATRIX) {
-      SV_LAUNCH(launch_matrix_pass(s->dt, ps.mx_k, s->ptr, s->n, ps.n_local, (const PassDescDev*)(db + pk.off_desc),
-                                   pk.desc_index[i], (int)ps.stages.size(), (const PassStageDev*)(db + pk.off_stage),
-                                   db + pk.off_pool, s->stream),
-                s->stream);
-      if (renorm > 0 && (since += ps.n_ops) >= renorm) {
-        if (sv_status r = renormalize(s)) return r;
-        since = 0;
-      }
-    } else {
-      SV_LAUNCH(launch_pass(s->dt, s->ptr, s->n, ps.n_local, (const PassDescDev*)(db + pk.off_desc),
-                            pk.desc_index[i], (const PassStageDev*)(db + pk.off_stage),
-                            (const PassItemDev*)(db + pk.off_items), db + pk.off_pool, pk.pass_lp[i] != 0,
-                            s->stream),
-                s->stream);
-    }
-  }
-  if (renorm > 0 && since > 0) return renormalize(s);
+  out->n_mx = (int)mx_list.size();
+  out->off_frags = host.size();
+  out->dev_bytes = host.size() + mx_list.size() * (size_t)kStageFragBytes;
   return SV_OK;
 }
 

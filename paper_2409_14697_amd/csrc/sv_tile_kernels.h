@@ -24,6 +24,9 @@ inline constexpr int pass_reg_bits(sv_dtype dt) { return dt == SV_C64 ? 5 : 4; }
 // A register stage of a tile pass applies, in this order (each part a block
 // of gates in program order that the planner proved may run in that order):
 //   1. optionally a dense 4x4 on register bits (1, 0)          (PSF_U2)
+//      (parts 1 to 3 and the register factors of part 4 are one 32 x 32
+//      matrix on the register bits, applied on the matrix cores, when the
+//      stage has an `mx` entry; complex64)
 //   2. nsub earlier layers (PassSubDev), each one 2x2 per register bit of
 //      its mask followed by a factor per register index: single-qubit gates
 //      separated by diagonal gates on register bits (the Hadamard and
@@ -144,10 +147,23 @@ struct alignas(16) PassStageDev {
   uint32_t pconst;                  // store map: constant XOR (local mask)
   uint32_t slot_mask;               // register bits whose 2x2 is not the identity
   uint32_t nsub;                    // earlier layers (<= kPassSubMax)
+  uint32_t mx;                      // matrix fragments of the stage's register part (kPassNoTable: none)
   // read by the stages that need them
   uint32_t colimg[kPassLocalMax];   // store map: image of local bit l (M e_l, a local mask)
   PassSubDev sub[kPassSubMax];
 };
+
+// Matrix fragments of a stage (complex64): its 32 x 32 matrix over the
+// register bits as operands of the bf16 matrix instructions, three bf16 parts
+// of every real number (sv_pass.hip, split_bf16).  Entry `mx` of the
+// program's fragment array; built on the device from the pool
+// (launch_stage_frags) after the program has been uploaded.
+constexpr int kStageFragBytes = 32 * 32 * 2 * 3 * 2;
+// List entry of launch_stage_frags: a stage index; kFragMatrixStage is set
+// for a stage of a matrix pass (a 32 x 32 matrix at pool entry u2).
+constexpr uint32_t kFragMatrixStage = 0x80000000u;
+hipError_t launch_stage_frags(const PassStageDev* stages, const uint32_t* list, int count, const void* pool,
+                              void* frags, hipStream_t s);
 
 // PassDescDev flag: the store can walk the tile in load order (the lowest
 // three 16-byte element bits keep their positions, so every run of 8 lanes
@@ -171,35 +187,41 @@ struct alignas(16) BatchItemDev {
   const PassStageDev* stages;
   const PassItemDev* items;
   const void* mats;
+  const void* frags;              // matrix fragments (complex64)
   uint64_t tile_begin;            // first global tile of this item (ascending)
   int32_t n;                      // qubits
   int32_t pass;                   // pass of the program to run
 };
 
-// Run pass items[i].pass of every item in one launch (all items share dt).
-// ladders: some item's pass holds PIT_LP or PIT_QG items (selects the kernel
-// variant that decodes them; the other variant carries none of their code).
-hipError_t launch_pass_batch(sv_dtype dt, const BatchItemDev* items, int count, uint64_t total_tiles, int max_m,
-                             bool ladders, hipStream_t s);
+// Where a complex64 pass runs the register parts of its stages: on the VALU,
+// on the matrix cores (every stage with a register part has an `mx` entry), or
+// on the matrix cores as the whole stage (a matrix pass).
+enum PassMatrix : char { kPassMatrixNone = 0, kPassMatrixTile = 1, kPassMatrixOnly = 2 };
 
-// Launch pass `pass` of a program already resident in device memory
-// (ladders: the pass holds PIT_LP or PIT_QG items).
+// Run pass items[i].pass of every item in one launch; all items share dt and
+// mx.  ladders: some item's pass holds PIT_LP or PIT_QG items.  (Both select
+// the kernel variant that holds the code the passes need.)
+hipError_t launch_pass_batch(sv_dtype dt, const BatchItemDev* items, int count, uint64_t total_tiles, int max_m,
+                             bool ladders, PassMatrix mx, hipStream_t s);
+
+// Launch pass `pass` of a program already resident in device memory: a tile
+// or permutation pass, or a complex64 matrix pass.
 hipError_t launch_pass(sv_dtype dt, void* psi, int n, int m, const PassDescDev* passes, int pass,
-                       const PassStageDev* stages, const PassItemDev* items, const void* mats, bool ladders,
-                       hipStream_t s);
+                       const PassStageDev* stages, const PassItemDev* items, const void* mats, const void* frags,
+                       bool ladders, PassMatrix mx, hipStream_t s);
 
 // --- matrix passes -----------------------------------------------------------
 // A matrix pass applies its stages, each a dense 2^k x 2^k op on k local bits
-// of the tile, on the matrix cores (complex64: k = 5, FP32 MFMA; complex128:
-// k = 4 or 5, FP64 MFMA).  Stage s (PassStageDev stage_first + s): q[b] = the
-// local bit of member bit b (b = 0 least significant), u2 = pool entry of the
-// matrix (row-major, rows and columns indexed by members), colimg and flags
-// as below.  Every other PassStageDev field is unused.  The tile and the A
-// fragments of all stages share one block's LDS, kMatrixPassLds bytes at
-// most; 2^(m-k) must be at least four column blocks of the instruction
-// (complex64 m >= 12; complex128 m >= k + 6).  The write-back stores every
-// element where it was loaded from (the planner gives matrix passes
-// wpos = lpos).
+// of the tile, on the matrix cores.  Stage s (PassStageDev stage_first + s):
+// q[b] = the local bit of member bit b (b = 0 least significant), u2 = pool
+// entry of the matrix (row-major, rows and columns indexed by members).
+// complex64 (k = 5): the stages run as tile-pass stages with matrix fragments
+// (launch_pass); every other PassStageDev field is unused.
+// complex128 (k = 4 or 5, FP64 MFMA; launch_matrix_pass): colimg and flags as
+// below.  The tile and the A fragments of all stages share one block's LDS,
+// kMatrixPassLds bytes at most; 2^(m-k) must be at least four column blocks of
+// the instruction (m >= k + 6).  The write-back stores every element where it
+// was loaded from (the planner gives matrix passes wpos = lpos).
 // Column order of a matrix stage: colimg[j] = the local bit of column bit j
 // (the columns are the tile's other local bits: first the lane bits, log2 of
 // the instruction's column count, then the wave bits, then the rest); wave w
@@ -212,15 +234,17 @@ constexpr uint32_t kMatrixStageSync = 1;
 constexpr int kMatrixWaves = 8;
 constexpr int kMatrixPassLds = 160 * 1024;
 constexpr int kMatrixStageTable = 768;  // bytes of a stage's address table
-// Stages of width k that fit beside a tile of 2^m amplitudes (A fragments:
-// 2^k x 2^k complex entries per stage, and the stage's address table).
+// Stages of width k in one pass: complex64 passes read their fragments from
+// global memory, complex128 passes hold them beside a tile of 2^m amplitudes
+// (A fragments: 2^k x 2^k complex entries per stage, and the stage's address
+// table).
 inline int matrix_pass_max_stages(sv_dtype dt, int k, int m) {
-  const size_t eb = dt == SV_C64 ? 8 : 16;
-  const size_t tile = ((size_t)1 << m) * eb, stage = ((size_t)1 << (2 * k)) * eb + kMatrixStageTable;
+  if (dt == SV_C64) return 64;
+  const size_t tile = (size_t)16 << m, stage = ((size_t)16 << (2 * k)) + kMatrixStageTable;
   return tile >= (size_t)kMatrixPassLds ? 0 : (int)(((size_t)kMatrixPassLds - tile) / stage);
 }
-hipError_t launch_matrix_pass(sv_dtype dt, int k, void* psi, int n, int m, const PassDescDev* passes, int pass,
-                              int n_stages, const PassStageDev* stages, const void* mats, hipStream_t s);
+hipError_t launch_matrix_pass(int k, void* psi, int n, int m, const PassDescDev* passes, int pass, int n_stages,
+                              const PassStageDev* stages, const void* mats, hipStream_t s);
 
 // --- dense k-qubit fused gate (3 <= k <= 6) ---------------------------------
 // m_dev: device copy of the 2^k x 2^k matrix, row-major interleaved, in the
