@@ -14,6 +14,7 @@
 // accumulates exactly one output bin.  Lanes that share a bin (they differ
 // only in unmeasured low bits) are combined in a fixed order through LDS, and
 // the per-chunk partial sums are added in chunk order by a second kernel.
+#include <algorithm>
 #include <mutex>
 
 #include "sv_device.h"
@@ -88,13 +89,24 @@ __global__ __launch_bounds__(kBlock) void k_probs_partial(const E* __restrict__ 
   }
 }
 
+// Sum the chunks' partials of every bin.  A block owns `bins` consecutive bins
+// (a power of two); its 256 / bins lanes per bin each add every so many chunks
+// in order, and the lanes' sums are added in order.  One thread per bin (as
+// with many bins) would add up to 4096 partials one load after another: 324 us
+// for the norm at N = 29, 5 us this way.
 __global__ __launch_bounds__(kBlock) void k_probs_final(const double* __restrict__ partial, uint64_t nbins,
-                                                        unsigned chunks, double* __restrict__ out) {
-  const uint64_t b = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (b >= nbins) return;
+                                                        unsigned chunks, unsigned bins, double* __restrict__ out) {
+  __shared__ double red[kBlock];
+  const unsigned b = threadIdx.x % bins, g = threadIdx.x / bins, lanes = kBlock / bins;
+  const double* src = partial + (uint64_t)blockIdx.x * bins + b;
   double s = 0.0;
-  for (unsigned c = 0; c < chunks; ++c) s += partial[(uint64_t)c * nbins + b];
-  out[b] = s;
+#pragma unroll 4
+  for (unsigned c = g; c < chunks; c += lanes) s += src[(uint64_t)c * nbins];
+  red[threadIdx.x] = s;
+  __syncthreads();
+  if (g) return;
+  for (unsigned k = 1; k < lanes; ++k) s += red[k * bins + b];
+  out[(uint64_t)blockIdx.x * bins + b] = s;
 }
 
 ProbGeo make_geo(int n, int m, const int* qubits, unsigned* chunks_out, uint64_t* qhi_blocks_out) {
@@ -184,9 +196,11 @@ hipError_t launch_probs(sv_dtype dt, const void* psi, int n, const int* qubits, 
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || chunks == 1) return e;
   const uint64_t nbins = 1ull << m;
-  const uint64_t blocks = (nbins + kBlock - 1) / kBlock;  // chunks > 1 only when 2^m partials fit 64 MiB
-  hipLaunchKernelGGL(k_probs_final, dim3((unsigned)blocks), dim3(kBlock), 0, s, (const double*)partial, nbins,
-                     chunks, out);
+  // bins per block: 32 keep the loads coalesced; all 256 when the chunks are
+  // few (a lane per bin then adds them without waiting long)
+  const uint64_t bins = std::min<uint64_t>(nbins, chunks <= 16 ? (uint64_t)kBlock : 32u);
+  hipLaunchKernelGGL(k_probs_final, dim3((unsigned)(nbins / bins)), dim3(kBlock), 0, s, (const double*)partial, nbins,
+                     chunks, (unsigned)bins, out);
   return hipGetLastError();
 }
 
