@@ -10,6 +10,7 @@ from __future__ import annotations
 import ctypes
 import os
 import re
+import struct
 from ctypes import POINTER, byref, c_char_p, c_double, c_int, c_int32, c_size_t, c_uint, c_uint64, c_void_p
 from typing import Iterable, List, Optional, Sequence, Tuple
 
@@ -40,6 +41,12 @@ class SvError(RuntimeError):
 class SvGate(ctypes.Structure):
     _fields_ = [("kind", c_int32), ("nq", c_int32), ("q", c_int32 * MAXQ), ("theta", c_double),
                 ("m", POINTER(c_double))]
+
+
+# the same record for struct.pack_into ("@": native sizes and alignment)
+_GATE = struct.Struct(f"@ii{MAXQ}idP")
+_PAD = (-1,) * MAXQ
+assert _GATE.size == ctypes.sizeof(SvGate)
 
 
 class SvOpts(ctypes.Structure):
@@ -136,21 +143,27 @@ def make_gates(gates: Sequence) -> tuple:
     ctypes array; returns (array, keepalive)."""
     arr = (SvGate * max(1, len(gates)))()
     keep = []
+    size = ctypes.sizeof(SvGate)
     for i, g in enumerate(gates):
-        sg = arr[i]
-        sg.kind = _kind_code(g.kind)
+        code = _kind_code(g.kind)
         qs = tuple(g.qubits)
-        sg.nq = len(qs)
-        for j in range(MAXQ):
-            sg.q[j] = qs[j] if j < len(qs) else -1
-        sg.theta = float(getattr(g, "theta", 0.0) or 0.0)
+        theta = float(getattr(g, "theta", 0.0) or 0.0)
         mat = getattr(g, "matrix", None)
-        if mat is not None and sg.kind == KIND["MATRIX"]:
+        addr = 0
+        if mat is not None and code == KIND["MATRIX"]:
             m = np.ascontiguousarray(np.asarray(mat, dtype=np.complex128)).view(np.float64)
             keep.append(m)
-            sg.m = m.ctypes.data_as(POINTER(c_double))
-        else:
-            sg.m = None
+            addr = m.__array_interface__["data"][0]
+        try:  # one write of the whole record (a write per ctypes field costs three times this)
+            _GATE.pack_into(arr, i * size, code, len(qs), *qs, *_PAD[len(qs):], theta, addr)
+        except struct.error:  # more than MAXQ qubits, numbers beyond 32 bits: field by field
+            sg = arr[i]
+            sg.kind = code
+            sg.nq = len(qs)
+            for j in range(MAXQ):
+                sg.q[j] = qs[j] if j < len(qs) else -1
+            sg.theta = theta
+            sg.m = ctypes.cast(c_void_p(addr), POINTER(c_double)) if addr else None
     return arr, keep
 
 

@@ -15,6 +15,16 @@
 namespace sv {
 
 void write_pool(unsigned char* dst, const cd* m, const uint8_t* raw, size_t count, bool f32) {
+  if (!raw) {  // plain numbers
+    if (f32) {
+      const double* src = reinterpret_cast<const double*>(m);
+      float* to = reinterpret_cast<float*>(dst);
+      for (size_t e = 0; e < 2 * count; ++e) to[e] = (float)src[e];
+    } else if (count) {
+      std::memcpy(dst, m, count * sizeof(cd));
+    }
+    return;
+  }
   for (size_t e = 0; e < count; ++e) {
     if (raw && raw[e]) {
       uint64_t w[2];
