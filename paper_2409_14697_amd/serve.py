@@ -295,8 +295,8 @@ class DeviceEngine:
         self.tile_qubits = lds_qubits or (13 if dtype == "c64" else 12)
         # states of at least matrix_qubits qubits are planned in mode AUTO:
         # fused dense ops in matrix passes where the cost model prefers them
-        # (each such pass is a launch of its own within the batched step; at
-        # these sizes one state fills the device by itself)
+        # (complex64: one batched launch for the step's matrix passes;
+        # complex128: a launch each)
         self.matrix_qubits = matrix_qubits
         self.stream = torch.cuda.current_stream()
         self.batcher = B.Batcher(self.stream)
