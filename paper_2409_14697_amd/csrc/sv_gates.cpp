@@ -93,6 +93,7 @@ Op op_from_gate(const sv_gate& g) {
 OpClass classify(const Op& op) {
   const size_t d = (size_t)1 << op.nq;
   bool diag = true, perm = true;
+  uint64_t taken = 0;  // columns of the ones so far (d <= 64)
   for (size_t r = 0; r < d; ++r) {
     int nz = 0;
     for (size_t c = 0; c < d; ++c) {
@@ -101,6 +102,8 @@ OpClass classify(const Op& op) {
         ++nz;
         if (r != c) diag = false;
         if (v != cd(1.0, 0.0)) perm = false;
+        if ((taken >> c) & 1u) perm = false;  // a row map that repeats rows is no permutation
+        taken |= 1ull << c;
       }
     }
     if (nz != 1) perm = false;
