@@ -125,7 +125,9 @@ typedef struct {
                                FP32, or split exactly into three bf16 parts);
                                default 1                                      */
   int32_t renorm_interval;  /* complex64 states: rescale to unit norm (FP64
-                               norm) every R dense ops; 0 = never; default 0   */
+                               norm) every R dense ops, at the end of the pass
+                               that holds the R-th (matrix passes then hold at
+                               most 10 ops); 0 = never; default 0             */
   int32_t mode;             /* sv_mode; default SV_MODE_AUTO                   */
   int32_t max_pass_ops;     /* tile passes: at most this many ops per pass, so
                                that passes of many states in one launch take

@@ -200,6 +200,9 @@ std::vector<Op> fuse_ops(std::vector<Op> in, int n, sv_dtype dt, int kmax, bool 
 // toward its final position (smaller gate blocks, fewer permutation passes).
 sv_status plan_tile_passes(const std::vector<Op>& ops, int n, sv_dtype dt, const sv_opts& o, sv_plan* p,
                            bool progress, int reserve = 0);
+// Ops of a matrix pass in a complex64 plan with a renorm_interval, at most:
+// renormalisation comes as many ops late at most.
+constexpr int kRenormPassOps = 10;
 // Matrix passes over a fused op list (logical = physical qubits): runs of
 // ops whose qubits, with the pinned low bits, fit one tile become one pass
 // of matrix-core stages; ops that do not pay off grouped run as sweeps.

@@ -369,6 +369,8 @@ double plan_matrix_passes(const std::vector<Op>& fused, int n, sv_dtype dt, cons
   const int pin = std::min(default_pinned_bits(dt), m);
   // four column blocks of the instruction per stage (one per wave)
   const int min_cols = dt == SV_C64 ? 7 : 6;
+  // plans that renormalise do it between passes, so their passes stay short
+  const int cap = dt == SV_C64 && o.renorm_interval > 0 ? kRenormPassOps : INT32_MAX;
   if (p) {
     p->ops.clear();
     p->op_pass.clear();
@@ -411,7 +413,7 @@ double plan_matrix_passes(const std::vector<Op>& fused, int n, sv_dtype dt, cons
         for (int i = 0; i < op.nq; ++i) extra += in_l[op.q[i]] ? 0 : 1;
         const int k2 = matrix_width(dt, std::max(kw, op.nq));
         if (count + extra <= m && m - k2 >= min_cols &&
-            (int)members.size() < matrix_pass_max_stages(dt, k2, m)) {
+            (int)members.size() < std::min(matrix_pass_max_stages(dt, k2, m), cap)) {
           for (int i = 0; i < op.nq; ++i)
             if (!in_l[op.q[i]]) {
               in_l[op.q[i]] = 1;
