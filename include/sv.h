@@ -304,7 +304,9 @@ typedef struct sv_batcher sv_batcher;  /* launches one pass of many states at on
 sv_status sv_program_bytes(const sv_plan *p, size_t *bytes);
 
 /* Upload the program of plan p (any mode: tile, permutation, matrix, dense
- * and sweep passes), stream-ordered on hip_stream (NULL = null stream).  A
+ * and sweep passes), stream-ordered on hip_stream (NULL = null stream): a copy
+ * and, for complex64 programs with matrix stages, a kernel that builds their
+ * operands behind the copied bytes of the buffer.  A
  * program does not renormalise: the plan's renorm_interval is not applied
  * to complex64 states run through a batcher.
  *   dev_buf : NULL -> the library allocates the device copy and frees it in
@@ -322,8 +324,9 @@ sv_status sv_program_info(const sv_program *prog, int32_t *n_qubits, sv_dtype *d
 
 /* Free a program.  When the library owns its device copy it first waits for
  * the upload stream; with a caller buffer it waits only for the program's
- * own upload (so that its host copy may be freed) and the caller orders the
- * reuse of the buffer after the work that reads it.  NULL is accepted. */
+ * own upload (the copy and the operand build: the last work of the library's
+ * own on the buffer) and the caller orders the reuse of the buffer after the
+ * passes it has enqueued.  NULL is accepted. */
 sv_status sv_program_destroy(sv_program *prog);
 
 /* A batcher owns its stream and small descriptor buffers. */

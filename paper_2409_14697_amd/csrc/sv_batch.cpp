@@ -22,7 +22,9 @@ struct sv_program {
   sv::PackedPlan packed;      // device image, kept for the async upload
   void* dev = nullptr;
   bool owned = false;
-  hipEvent_t uploaded = nullptr;  // after the upload: the host copy may be freed
+  // after the copy and the fragment build: the host copy may be freed, and no
+  // work of the program's own uses the device buffer any more
+  hipEvent_t uploaded = nullptr;
   hipStream_t stream = nullptr;
 };
 
@@ -137,11 +139,12 @@ sv_status sv_program_create(const sv_plan* p, void* dev_buf, size_t buf_bytes, v
     prog->uploaded = nullptr;
     st = fail(SV_ERR_DEVICE, "hipEventCreate failed");
   }
-  if (st == SV_OK && (hipMemcpyAsync(prog->dev, prog->packed.host.data(), prog->packed.host.size(), hipMemcpyHostToDevice,
-                                     prog->stream) != hipSuccess ||
-                      hipEventRecord(prog->uploaded, prog->stream) != hipSuccess))
+  if (st == SV_OK && hipMemcpyAsync(prog->dev, prog->packed.host.data(), prog->packed.host.size(), hipMemcpyHostToDevice,
+                                    prog->stream) != hipSuccess)
     st = fail(SV_ERR_DEVICE, "program upload failed");
   if (st == SV_OK) st = build_fragments(prog->packed, (unsigned char*)prog->dev, prog->stream);
+  if (st == SV_OK && hipEventRecord(prog->uploaded, prog->stream) != hipSuccess)
+    st = fail(SV_ERR_DEVICE, "program upload failed");
   if (st != SV_OK) {
     (void)hipStreamSynchronize(prog->stream);
     if (prog->owned) (void)hipFree(prog->dev);
@@ -169,7 +172,7 @@ sv_status sv_program_destroy(sv_program* prog) {
   if (prog->owned) {
     if (hipStreamSynchronize(prog->stream) != hipSuccess) st = fail(SV_ERR_DEVICE, "stream sync failed");
     (void)hipFree(prog->dev);
-  } else if (hipEventSynchronize(prog->uploaded) != hipSuccess) {  // the upload may still read the host copy
+  } else if (hipEventSynchronize(prog->uploaded) != hipSuccess) {  // the upload may still use both copies
     st = fail(SV_ERR_DEVICE, "event sync failed");
   }
   (void)hipEventDestroy(prog->uploaded);
