@@ -275,19 +275,27 @@ sv_status sv_batcher_run(sv_batcher* b, int count, sv_state* const* states, cons
   }
   BatchItemDev* at = (BatchItemDev*)b->host[k];
   for (const Group& gr : groups) at = std::copy(gr.items.begin(), gr.items.end(), at);
-  SV_HIP_TRY(hipMemcpyAsync(b->dev[k], b->host[k], bytes, hipMemcpyHostToDevice, b->stream));
-  const BatchItemDev* dev = (const BatchItemDev*)b->dev[k];
-  for (int v = 0; v < 3; ++v) {
-    const Group& gr = groups[v];
-    if (gr.items.empty()) continue;
-    SV_LAUNCH(launch_pass_batch(dt, dev, (int)gr.items.size(), gr.tiles, gr.max_m, gr.ladders, (PassMatrix)v,
-                                b->stream),
-              b->stream);
-    dev += gr.items.size();
+  auto enqueue = [&]() -> sv_status {
+    SV_HIP_TRY(hipMemcpyAsync(b->dev[k], b->host[k], bytes, hipMemcpyHostToDevice, b->stream));
+    const BatchItemDev* dev = (const BatchItemDev*)b->dev[k];
+    for (int v = 0; v < 3; ++v) {
+      const Group& gr = groups[v];
+      if (gr.items.empty()) continue;
+      SV_LAUNCH(launch_pass_batch(dt, dev, (int)gr.items.size(), gr.tiles, gr.max_m, gr.ladders, (PassMatrix)v,
+                                  b->stream),
+                b->stream);
+      dev += gr.items.size();
+    }
+    return SV_OK;
+  };
+  const sv_status st = enqueue();
+  // also after a failure: what was enqueued before it still reads the slot
+  b->used[k] = hipEventRecord(b->done[k], b->stream) == hipSuccess;
+  if (!b->used[k]) {
+    (void)hipStreamSynchronize(b->stream);
+    return st != SV_OK ? st : fail(SV_ERR_DEVICE, "hipEventRecord failed");
   }
-  SV_HIP_TRY(hipEventRecord(b->done[k], b->stream));
-  b->used[k] = true;
-  return SV_OK;
+  return st;
 }
 
 sv_status sv_batcher_probs(sv_batcher* b, const sv_state* s, const int32_t* qubits, int m, double* out_dev) {

@@ -207,11 +207,47 @@ void scenario_program() {
   }
 }
 
+// A step of several launches fails after its first: the descriptors it has
+// enqueued are still read when its slot comes round again.
+void scenario_batcher() {
+  const int n = 13;
+  sv_gate g[2] = {gate(SV_G_RY, {3}, 0.2), gate(SV_G_RX, {8}, 0.4)};
+  sv_opts o;
+  sv_default_opts(&o);
+  o.mode = SV_MODE_PASS;
+  sv_plan* plans[2] = {plan(n, SV_MODE_PASS, 5), nullptr};  // on the matrix cores, on the VALU
+  expect(sv_fuse(n, SV_C64, g, 2, &o, &plans[1]), SV_OK);
+  sv_program* progs[2];
+  sv_state* states[2];
+  for (int i = 0; i < 2; ++i) {
+    expect(sv_program_create(plans[i], nullptr, 0, nullptr, &progs[i]), SV_OK);
+    expect(sv_create(n, SV_C64, nullptr, nullptr, SV_NO_INIT, &states[i]), SV_OK);
+  }
+  sv_batcher* b = nullptr;
+  expect(sv_batcher_create(nullptr, &b), SV_OK);
+  const int32_t pass[2] = {0, 0};
+  for (int failing = 0; failing < 2; ++failing) {
+    batch_launches = 0;
+    fail_launch = failing;
+    expect(sv_batcher_run(b, 2, states, progs, pass), SV_ERR_DEVICE);
+    fail_launch = -1;
+    for (int i = 0; i < 9; ++i) expect(sv_batcher_run(b, 2, states, progs, pass), SV_OK);
+    if (batch_launches != failing + 1 + 18) fault("a step is not two launches");
+  }
+  expect(sv_batcher_destroy(b), SV_OK);
+  for (int i = 0; i < 2; ++i) {
+    expect(sv_program_destroy(progs[i]), SV_OK);
+    expect(sv_destroy(states[i]), SV_OK);
+    sv_plan_destroy(plans[i]);
+  }
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   const std::string s = argc > 1 ? argv[1] : "";
   if (s == "program") scenario_program();
+  else if (s == "batcher") scenario_batcher();
   else fault("unknown scenario");
   return faults ? 1 : 0;
 }
