@@ -56,23 +56,37 @@ sv_status upload(sv_state* s, const void* host, size_t bytes, size_t dev_bytes, 
     SV_HIP_TRY(hipEventSynchronize(s->up_done));
     s->up_pending = false;
   }
+  auto capacity = [](size_t need) {
+    size_t cap = 1 << 16;
+    while (cap < need) cap <<= 1;
+    return cap;
+  };
   if (dev_bytes > s->up_bytes) {
     if (s->up_dev) {
       SV_HIP_TRY(hipStreamSynchronize(s->stream));
       SV_HIP_TRY(hipFree(s->up_dev));
-      SV_HIP_TRY(hipHostFree(s->up_host));
-      s->up_dev = s->up_host = nullptr;
+      s->up_dev = nullptr;
       s->up_bytes = 0;
     }
-    size_t cap = 1 << 16;
-    while (cap < dev_bytes) cap <<= 1;
-    if (hipMalloc(&s->up_dev, cap) != hipSuccess) return fail(SV_ERR_NOMEM, "cannot allocate upload buffer");
-    if (hipHostMalloc(&s->up_host, cap, hipHostMallocDefault) != hipSuccess) {
-      (void)hipFree(s->up_dev);
+    const size_t cap = capacity(dev_bytes);
+    if (hipMalloc(&s->up_dev, cap) != hipSuccess) {
       s->up_dev = nullptr;
-      return fail(SV_ERR_NOMEM, "cannot allocate pinned staging buffer");
+      return fail(SV_ERR_NOMEM, "cannot allocate upload buffer");
     }
     s->up_bytes = cap;
+  }
+  if (bytes > s->up_host_bytes) {  // (the last copy from it is over)
+    if (s->up_host) {
+      SV_HIP_TRY(hipHostFree(s->up_host));
+      s->up_host = nullptr;
+      s->up_host_bytes = 0;
+    }
+    const size_t cap = capacity(bytes);
+    if (hipHostMalloc(&s->up_host, cap, hipHostMallocDefault) != hipSuccess) {
+      s->up_host = nullptr;
+      return fail(SV_ERR_NOMEM, "cannot allocate pinned staging buffer");
+    }
+    s->up_host_bytes = cap;
   }
   std::memcpy(s->up_host, host, bytes);
   SV_HIP_TRY(hipMemcpyAsync(s->up_dev, s->up_host, bytes, hipMemcpyHostToDevice, s->stream));

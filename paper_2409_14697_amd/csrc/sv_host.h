@@ -165,7 +165,7 @@ struct sv_state {
   // matrix uploads: pinned host staging + device buffer
   void* up_host = nullptr;
   void* up_dev = nullptr;
-  size_t up_bytes = 0;
+  size_t up_bytes = 0, up_host_bytes = 0;
   hipEvent_t up_done = nullptr;
   bool up_pending = false;
 };

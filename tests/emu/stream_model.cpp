@@ -242,12 +242,43 @@ void scenario_batcher() {
   }
 }
 
+// Pinned staging memory holds what is staged, not the fragments that are built
+// on the device behind it.
+void scenario_staging() {
+  sv_state* st = nullptr;
+  expect(sv_create(13, SV_C64, nullptr, nullptr, SV_NO_INIT, &st), SV_OK);
+  for (int mode : {(int)SV_MODE_PASS, (int)SV_MODE_MATRIX, (int)SV_MODE_PASS}) {
+    sv_plan* p = plan(13, mode, 5);
+    sv::PackedPlan pk;
+    expect(sv::pack_plan(p, &pk), SV_OK);
+    pinned_sizes.clear();
+    queue.clear();
+    finished = 0;
+    expect(sv_apply_plan(st, p), SV_OK);
+    for (size_t n : pinned_sizes)
+      if (n > 65536 && n >= 2 * pk.host.size())
+        fault("staging buffer of " + std::to_string(n) + " bytes for " + std::to_string(pk.host.size()));
+    // the device buffer holds the image and the fragments
+    for (const Work& w : queue)
+      for (const Span& s : w.uses) {
+        bool inside = false;
+        for (const auto& a : allocs)
+          inside = inside || (s.at >= (unsigned char*)a.first && s.at + s.bytes <= (unsigned char*)a.first + a.second);
+        if (!inside) fault(std::string(w.what) + " uses memory outside the buffers");
+      }
+    (void)hipStreamSynchronize(nullptr);
+    sv_plan_destroy(p);
+  }
+  expect(sv_destroy(st), SV_OK);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   const std::string s = argc > 1 ? argv[1] : "";
   if (s == "program") scenario_program();
   else if (s == "batcher") scenario_batcher();
+  else if (s == "staging") scenario_staging();
   else fault("unknown scenario");
   return faults ? 1 : 0;
 }
