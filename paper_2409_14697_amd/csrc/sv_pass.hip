@@ -261,8 +261,10 @@ __device__ __forceinline__ void layer(cplx<R>* v, cptr<cplx<R>> M, uint32_t form
 // complex multiplication (measured; the accumulator rounds once per sixteen
 // products instead of once per two, and Yi = P3 - P1 - P2 cancels).  Four
 // real products are formed (P1 = Ur Xr, P2 = Ui Xi, Yi = Ur Xi + Ui Xr).
-// Infinite and NaN amplitudes leave their whole group not finite, as any
-// complex product with them does.
+// An infinite or NaN amplitude leaves its whole column not finite (zero times
+// infinity is not a number), as FP32 products with the 32 x 32 matrix do.  The
+// layers of a tile stage mix an amplitude only with the members that their
+// gates reach, so a wave with such an amplitude runs them one by one.
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -352,11 +354,13 @@ __device__ __forceinline__ void swap_halves(float& a, float& b) {
 }
 
 // v <- U v for the 32 register amplitudes of every lane (all 64 lanes run
-// it).  A lane holds one column; the instruction wants 32 columns, each
+// it); false, with v undefined, if one of the wave's amplitudes is not finite
+// (the zeros of U would spread it over its whole column).  A lane holds one
+// column; the instruction wants 32 columns, each
 // spread over two lanes: exchanging the halves of the wave turns the 64
 // columns into two column blocks and the results back into columns, with
 // one lane exchange per pair of registers and no LDS traffic.
-__device__ __forceinline__ void mx_apply(cplx<float>* v, gptr<const u32x4> frags) {
+__device__ __forceinline__ bool mx_apply(cplx<float>* v, gptr<const u32x4> frags) {
   const gptr<const u32x4> fr = frags + (threadIdx.x & 63u);
   f32x16 p1[2], p2[2], p3[2];
 #pragma unroll
@@ -424,6 +428,9 @@ __device__ __forceinline__ void mx_apply(cplx<float>* v, gptr<const u32x4> frags
     v[row].im = a;
     v[row + 4].im = b;
   }
+  // every row takes in every part of every member, and the residual of an
+  // infinity is not a number: one result of the column tells
+  return __builtin_amdgcn_ballot_w64(v[0].im != v[0].im) == 0;
 }
 
 // The three bf16 parts of an FP64 matrix entry, in the low halves.
@@ -1051,8 +1058,9 @@ __device__ __forceinline__ void matrix_stages(const TileRef<float>& T, flt2* til
 
 // Kernel variants (each carries only the code its passes need).  LP: the
 // pass holds fixed-point phase items.  MX_NONE: the register parts of its
-// stages run on the VALU; MX_TILE: on the matrix cores; MX_ONLY: a matrix
-// pass, whose stages are matrices and nothing else.
+// stages run on the VALU; MX_TILE: on the matrix cores (and on the VALU in
+// waves whose amplitudes the split cannot hold); MX_ONLY: a matrix pass, whose
+// stages are matrices and nothing else.
 enum { MX_NONE = 0, MX_TILE = 1, MX_ONLY = 2 };
 
 template <typename R, bool LP, int MX>
@@ -1115,35 +1123,49 @@ __device__ __forceinline__ void tile_stages(const TileRef<R>& T, typename dev_el
       const uint32_t xg = own ? group_bits<RB>(t, S) : 0u;
       const uint32_t sx = swz<LB>(xg);
       cplx<R> v[NR];
+      auto gather = [&](uint32_t at) {
 #pragma unroll
-      for (int r = 0; r < NR; ++r) {
-        uint32_t o = sx;
+        for (int r = 0; r < NR; ++r) {
+          uint32_t o = at;
 #pragma unroll
-        for (int b = 0; b < RB; ++b)
-          if ((r >> b) & 1) o ^= sbit[b];
-        const E e = tile[o];
-        v[r] = cplx<R>{e.x, e.y};
-      }
-      bool folded = false;  // the register factors are part of the stage's matrix
-      if constexpr (MX != MX_NONE) {
-        if (S.mx() != kPassNoTable) {
-          mx_apply(v, as_global(reinterpret_cast<const u32x4*>(T.frags)) + (size_t)S.mx() * (kStageFragBytes / 16));
-          folded = true;
+          for (int b = 0; b < RB; ++b)
+            if ((r >> b) & 1) o ^= sbit[b];
+          const E e = tile[o];
+          v[r] = cplx<R>{e.x, e.y};
         }
-      } else {
-        if (flags & PSF_U2) op_u2<R>(v, mats + S.u2());
-        // the earlier layers (2x2s, then register factors), then the last one;
-        // one copy of the layer code serves all of them
-        const cptr<PassSubDev> subs = (cptr<PassSubDev>)((cptr<uint32_t>)S.p + offsetof(PassStageDev, sub) / 4);
-        for (uint32_t li = 0; li <= S.nsub(); ++li) {
-          const bool last = li == S.nsub();
-          const PassSubDev L = last ? PassSubDev{S.form(), S.slot_mask(), S.slots(), kPassNoTable} : cload(subs + li);
+      };
+      gather(sx);
+      // the register part on the VALU: the 4x4, the earlier layers (2x2s, then
+      // register factors), then the last one; one copy of the layer code
+      // serves all layers
+      auto register_part = [&](const Stage& F) {
+        if (F.flags() & PSF_U2) op_u2<R>(v, mats + F.u2());
+        const cptr<PassSubDev> subs = (cptr<PassSubDev>)((cptr<uint32_t>)F.p + offsetof(PassStageDev, sub) / 4);
+        for (uint32_t li = 0; li <= F.nsub(); ++li) {
+          const bool last = li == F.nsub();
+          const PassSubDev L = last ? PassSubDev{F.form(), F.slot_mask(), F.slots(), kPassNoTable} : cload(subs + li);
           if (L.form) layer<R>(v, mats + L.slots, L.form);
           if (L.dr != kPassNoTable) {
             const cptr<cplx<R>> D = mats + L.dr;
 #pragma unroll
             for (int r = 0; r < NR; ++r) v[r] = cmul(cget(D, r), v[r]);
           }
+        }
+      };
+      bool folded = false;  // the register factors are part of the stage's matrix
+      if constexpr (MX == MX_NONE) {
+        register_part(S);
+      } else if (S.mx() != kPassNoTable) {
+        folded = mx_apply(v, as_global(reinterpret_cast<const u32x4*>(T.frags)) + (size_t)S.mx() * (kStageFragBytes / 16));
+        if (__builtin_expect(!folded, 0)) {
+          // the tile still holds the wave's amplitudes (opaque copies: what
+          // this rare branch needs does not occupy registers before it)
+          uint32_t at = sx;
+          asm volatile("" : "+v"(at));
+          gather(at);
+          cptr<PassStageDev> sp = S.p;
+          asm volatile("" : "+s"(sp));
+          register_part(load_stage(sp));
         }
       }
       if (flags & PSF_LANE) {
