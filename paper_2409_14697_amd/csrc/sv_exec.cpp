@@ -6,7 +6,7 @@ namespace sv {
 
 sv_status build_fragments(const PackedPlan& pk, unsigned char* dev, hipStream_t s) {
   if (!pk.n_mx) return SV_OK;
-  SV_LAUNCH(launch_stage_frags((const PassStageDev*)(dev + pk.off_stage), (const uint32_t*)(dev + pk.off_list), pk.n_mx,
+  SV_LAUNCH(launch_stage_frags((PassStageDev*)(dev + pk.off_stage), (const uint32_t*)(dev + pk.off_list), pk.n_mx,
                                dev + pk.off_pool, dev + pk.off_frags, s),
             s);
   return SV_OK;

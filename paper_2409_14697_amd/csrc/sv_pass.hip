@@ -248,12 +248,20 @@ __device__ __forceinline__ void layer(cplx<R>* v, cptr<cplx<R>> M, uint32_t form
   if constexpr (Regs<R>::RB > 4) slot<4>(v, M, forms);
 }
 
+// s_waitcnt with only the vector-memory counter (gfx9 encoding: expcnt and
+// lgkmcnt at their no-wait values).
+template <int N>
+__device__ __forceinline__ void wait_vm() {
+  static_assert(N >= 0 && N < 64, "vmcnt range");
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
+}
+
 // ---- FP32 products on the bf16 matrix cores --------------------------------
 // The FP32 matrix instructions run at 1/16 of the bf16 rate (64 against 1024
 // flops per cycle and SIMD).  An FP32 value is exactly the sum of three bf16
 // values, h + m + l (the top 8 bits, the next 8 rounded to nearest, the
-// rest), each with the full FP32 exponent range, and products of bf16 values
-// are exact in the FP32 accumulator; of the nine part products of u x the
+// rest), while the rest stays within bf16's range (see below), and products of
+// bf16 values are exact in the FP32 accumulator; of the nine part products of u x the
 // six of relative size >= 2^-17 are summed (smallest first), the dropped
 // ones are below 2^-25 |u x|, less than the rounding of one FP32 product.
 // Error against FP64 for Haar 32 x 32 blocks on Gaussian columns: 5.1e-8
@@ -268,6 +276,21 @@ __device__ __forceinline__ void layer(cplx<R>* v, cptr<cplx<R>> M, uint32_t form
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// Range.  bf16 ends 16 binades above the last bit of the smallest FP32 values,
+// so amplitudes are split as 2^16 x: exact below 2^112; beyond, the parts are
+// not numbers and the results show it.  A tile stage scales its own
+// amplitudes and has fragments of 2^-16 U; in a matrix pass the first stage
+// scales them, the last one's fragments scale back and the others' are of U.
+// These hold matrix entries from kMxSmallEntry up with all their bits; a stage
+// with smaller nonzero entries is marked (kFragSmallEntries): a tile stage then
+// runs on the VALU, a matrix stage has fragments 2^32 times as large and scales
+// its results back, which must stay finite.  Measured: 64 VALU instructions more
+// per wave and scaling stage, QFT N = 28 6.81 -> 6.89 ms; brickwork N = 30 stays
+// at 136 ms (138 with a scaling in every stage of a pass).
+constexpr float kMxScale = 0x1p16f, kMxUnscale = 0x1p-16f;
+constexpr float kMxSmallScale = 0x1p32f, kMxSmallUnscale = 0x1p-32f;
+constexpr double kMxSmallEntry = 0x1p-94;
 
 // The parts of (x, y), x in the low halves.  (v_dot2_f32_bf16 would form a
 // residual without unpacking, 7 instructions per pair against 11, but it does
@@ -304,16 +327,18 @@ static_assert(frag_at(3, 0, 0) * 16 == kStageFragBytes, "fragment size");
 struct MxOperand {
   u32x4 re[3], im[3];  // part
 };
+template <bool SCALE>
 __device__ __forceinline__ MxOperand mx_split(const flt2* x) {
+  const float s = SCALE ? kMxScale : 1.f;
   MxOperand b;
 #pragma unroll
   for (int d = 0; d < 4; ++d) {
     const flt2 x0 = x[2 * d], x1 = x[2 * d + 1];
     uint32_t p[3];
-    split_bf16(x0.x, x1.x, &p[0], &p[1], &p[2]);
+    split_bf16(s * x0.x, s * x1.x, &p[0], &p[1], &p[2]);
 #pragma unroll
     for (int k = 0; k < 3; ++k) b.re[k][d] = p[k];
-    split_bf16(x0.y, x1.y, &p[0], &p[1], &p[2]);
+    split_bf16(s * x0.y, s * x1.y, &p[0], &p[1], &p[2]);
 #pragma unroll
     for (int k = 0; k < 3; ++k) b.im[k][d] = p[k];
   }
@@ -353,6 +378,19 @@ __device__ __forceinline__ void swap_halves(float& a, float& b) {
   b = __builtin_bit_cast(float, y);
 }
 
+// The fragments of a stage (its `mx` entry).
+__device__ __forceinline__ gptr<const u32x4> mx_frags(const void* frags, uint32_t mx) {
+  return as_global(reinterpret_cast<const u32x4*>(frags)) + (size_t)(mx & ~kFragSmallEntries) * (kStageFragBytes / 16);
+}
+// Results x, y of fragments with small entries, scaled back; returns the largest
+// magnitude (not a number if one of them is not).
+__device__ __forceinline__ float mx_unscale(float largest, float& x, float& y) {
+  largest = __builtin_elementwise_maximum(__builtin_elementwise_maximum(largest, __builtin_fabsf(x)), __builtin_fabsf(y));
+  x *= kMxSmallUnscale;
+  y *= kMxSmallUnscale;
+  return largest;
+}
+
 // v <- U v for the 32 register amplitudes of every lane (all 64 lanes run
 // it); false, with v undefined, if one of the wave's amplitudes is not finite
 // (the zeros of U would spread it over its whole column).  A lane holds one
@@ -360,8 +398,8 @@ __device__ __forceinline__ void swap_halves(float& a, float& b) {
 // spread over two lanes: exchanging the halves of the wave turns the 64
 // columns into two column blocks and the results back into columns, with
 // one lane exchange per pair of registers and no LDS traffic.
-__device__ __forceinline__ bool mx_apply(cplx<float>* v, gptr<const u32x4> frags) {
-  const gptr<const u32x4> fr = frags + (threadIdx.x & 63u);
+__device__ __forceinline__ bool mx_apply(cplx<float>* v, const void* frags, uint32_t mx) {
+  const gptr<const u32x4> fr = mx_frags(frags, mx) + (threadIdx.x & 63u);
   f32x16 p1[2], p2[2], p3[2];
 #pragma unroll
   for (int cb = 0; cb < 2; ++cb) p1[cb] = p2[cb] = p3[cb] = f32x16{};
@@ -374,10 +412,10 @@ __device__ __forceinline__ bool mx_apply(cplx<float>* v, gptr<const u32x4> frags
       for (int h = 0; h < 2; ++h) {  // members 16 ks + 8 h + 2 d, + 1
         const cplx<float> x0 = v[16 * ks + 8 * h + 2 * d], x1 = v[16 * ks + 8 * h + 2 * d + 1];
         uint32_t p[3];
-        split_bf16(x0.re, x1.re, &p[0], &p[1], &p[2]);
+        split_bf16(kMxScale * x0.re, kMxScale * x1.re, &p[0], &p[1], &p[2]);
 #pragma unroll
         for (int k = 0; k < 3; ++k) br[h][k][d] = p[k];
-        split_bf16(x0.im, x1.im, &p[0], &p[1], &p[2]);
+        split_bf16(kMxScale * x0.im, kMxScale * x1.im, &p[0], &p[1], &p[2]);
 #pragma unroll
         for (int k = 0; k < 3; ++k) bi[h][k][d] = p[k];
       }
@@ -411,7 +449,7 @@ __device__ __forceinline__ bool mx_apply(cplx<float>* v, gptr<const u32x4> frags
 #pragma unroll
       for (int q = 0; q < 48; ++q) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);
       }
     }
   }
@@ -447,15 +485,16 @@ __device__ __forceinline__ void split_entry(double x, uint32_t* p) {
 
 // Build the matrix fragments of the listed stages, one block per stage: the
 // register part (4x4, layers, register factors) applied to the columns of
-// the identity in FP64, or the matrix of a matrix-pass stage.  Runs once per
-// upload of a program; a few microseconds, latency-bound.
-__global__ __launch_bounds__(kBlock) void k_stage_frags(const PassStageDev* __restrict__ stages,
+// the identity in FP64, or the matrix of a matrix-pass stage (the entries of
+// either are FP32 numbers of the pool).  Marks the stages with small entries.
+// Runs once per upload of a program; a few microseconds, latency-bound.
+__global__ __launch_bounds__(kBlock) void k_stage_frags(PassStageDev* __restrict__ stages,
                                                         const uint32_t* __restrict__ list,
                                                         const cplx<float>* __restrict__ mats, uint32_t* __restrict__ frags) {
   constexpr int D = 32, NG = kBlock / D;
   __shared__ cplx<double> U[D][D + 1];
   const uint32_t e = list[blockIdx.x];
-  const cptr<PassStageDev> sp = as_const(stages) + (e & ~kFragMatrixStage);
+  const cptr<PassStageDev> sp = as_const(stages) + (e & kFragStage);
   const PassStageDev S = cload(sp);
   const uint32_t c = threadIdx.x % D, g = threadIdx.x / D;
   auto entry = [&](uint32_t i) { return cplx<double>{(double)mats[i].re, (double)mats[i].im}; };
@@ -499,16 +538,23 @@ __global__ __launch_bounds__(kBlock) void k_stage_frags(const PassStageDev* __re
     }
   }
   __syncthreads();
+  bool small = false;  // nonzero entries below kMxSmallEntry
+  for (uint32_t r = g; r < (uint32_t)D; r += NG)
+    for (const double x : {U[r][c].re, U[r][c].im}) small = small || (x != 0.0 && fabs(x) < kMxSmallEntry);
+  small = __syncthreads_or(small);
+  if (small && threadIdx.x == 0) stages[e & kFragStage].mx = S.mx | kFragSmallEntries;
+  const bool unscales = !(e & kFragMatrixStage) || (e & kFragLastStage);
+  const double scale = (unscales ? (double)kMxUnscale : 1.0) * (small ? (double)kMxSmallScale : 1.0);
   uint32_t* out = frags + (size_t)blockIdx.x * (kStageFragBytes / 4);
   for (uint32_t f = threadIdx.x; f < 512; f += kBlock) {  // k-step, lane, register of the fragment
     const uint32_t ks = f / 256, l = (f / 4) % 64, d = f % 4;
     const cplx<double> a = U[l % 32][16 * ks + 8 * (l / 32) + 2 * d], b = U[l % 32][16 * ks + 8 * (l / 32) + 2 * d + 1];
     uint32_t x[3], y[3];
-    split_entry(a.re, x);
-    split_entry(b.re, y);
+    split_entry(scale * a.re, x);
+    split_entry(scale * b.re, y);
     for (int p = 0; p < 3; ++p) out[(frag_at(p, 0, 0) + ks * 64 + l) * 4 + d] = x[p] | (y[p] << 16);
-    split_entry(a.im, x);
-    split_entry(b.im, y);
+    split_entry(scale * a.im, x);
+    split_entry(scale * b.im, y);
     for (int p = 0; p < 3; ++p) out[(frag_at(p, 1, 0) + ks * 64 + l) * 4 + d] = x[p] | (y[p] << 16);
   }
 }
@@ -965,27 +1011,68 @@ __device__ __forceinline__ void mx_write(const MxGeo& g, const MxProducts& p, ui
   }
 }
 
+// The results of fragments with small entries of a column block, scaled back;
+// returns whether one is not finite.
+__device__ __forceinline__ bool mx_unscale_block(const MxGeo& g, uint32_t at, flt2* tile) {
+  float largest = 0.f;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    flt2 y = tile[at ^ mx_out(g, r)];
+    float re = y.x, im = y.y;
+    largest = mx_unscale(largest, re, im);
+    tile[at ^ mx_out(g, r)] = flt2{re, im};
+  }
+  return !(largest < __builtin_inff());
+}
+
+// The stage in FP32 on a column block, one product after the other, in place.
+__device__ __forceinline__ void mx_stage_fp32(const MxGeo& g, cptr<cplx<float>> U, uint32_t out, flt2* tile) {
+  const uint32_t half = (threadIdx.x >> 5) & 1u;
+  const uint32_t col = out ^ (half ? g.sb[2] : 0u);
+  const gptr<const flt2> u = as_global(reinterpret_cast<const flt2*>((uint64_t)U)) + 4 * 32 * half;
+  flt2 y[16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) y[r] = flt2{0.f, 0.f};
+#pragma unroll 1
+  for (uint32_t k = 0; k < 32; ++k) {
+    uint32_t at = col;
+#pragma unroll
+    for (int b = 0; b < 5; ++b) at ^= ((k >> b) & 1u) ? g.sb[b] : 0u;
+    const flt2 x = tile[at];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const flt2 a = u[(8 * (r / 4) + r % 4) * 32 + k];
+      y[r].x = __builtin_fmaf(-a.y, x.y, __builtin_fmaf(a.x, x.x, y[r].x));
+      y[r].y = __builtin_fmaf(a.y, x.x, __builtin_fmaf(a.x, x.y, y[r].y));
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) tile[out ^ mx_out(g, r)] = y[r];
+}
+
 // One stage on a wave's two column blocks.  A matrix instruction (32 cycles)
 // leaves room for six VALU instructions of the two waves of a SIMD (measured),
 // so the second k-step is split beside the first one's products.  Both blocks
 // share each A fragment: reading them once per block instead costs more than
 // finishing one block early gains (N = 28, 6 stages: 2.31 against 2.20 ms).
-template <bool PAIRS>
-__device__ __forceinline__ void mx_stage_two(const MxGeo& g, gptr<const u32x4> fr, flt2* tile) {
+// Returns whether the lane's columns hold what the split cannot (of the last
+// stage: it shows by then).
+template <bool PAIRS, bool FIRST>
+__device__ __forceinline__ bool mx_stage_two(const MxGeo& g, gptr<const u32x4> fr, flt2* tile) {
   flt2 x0[16], x1[16];
   mx_read<PAIRS>(g, tile, g.in0, x0);
   mx_read<PAIRS>(g, tile, g.in0 ^ g.next, x1);
   MxProducts p0, p1;
-  const MxOperand b0 = mx_split(x0), b1 = mx_split(x1);
+  const MxOperand b0 = mx_split<FIRST>(x0), b1 = mx_split<FIRST>(x1);
   const MxOperand* const b[2] = {&b0, &b1};
   MxProducts* const p[2] = {&p0, &p1};
   __builtin_amdgcn_sched_barrier(0);
   mx_products<2>(b, fr, 0, p);
-  const MxOperand c0 = mx_split(x0 + 8), c1 = mx_split(x1 + 8);
+  const MxOperand c0 = mx_split<FIRST>(x0 + 8), c1 = mx_split<FIRST>(x1 + 8);
 #pragma unroll
   for (int i = 0; i < 48; ++i) {
     __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-    __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);  // VALU
+    __builtin_amdgcn_sched_group_barrier(0x002, FIRST ? 5 : 4, 0);  // VALU
   }
   __builtin_amdgcn_sched_barrier(0);
   const MxOperand* const c[2] = {&c0, &c1};
@@ -993,33 +1080,67 @@ __device__ __forceinline__ void mx_stage_two(const MxGeo& g, gptr<const u32x4> f
   __builtin_amdgcn_sched_barrier(0);
   mx_write<PAIRS>(g, p0, g.out0, tile);
   mx_write<PAIRS>(g, p1, g.out0 ^ g.next, tile);
+  __builtin_amdgcn_sched_barrier(0);  // (the second block's products need not end before the first is written)
+  return p0.im[0] != p0.im[0] || p1.im[0] != p1.im[0];  // as in mx_apply, one result of a column tells
 }
-template <bool PAIRS>
-__device__ __forceinline__ void mx_stage_one(const MxGeo& g, gptr<const u32x4> fr, flt2* tile) {
+template <bool PAIRS, bool FIRST>
+__device__ __forceinline__ bool mx_stage_one(const MxGeo& g, gptr<const u32x4> fr, flt2* tile) {
   flt2 x[16];
   mx_read<PAIRS>(g, tile, g.in0, x);
   MxProducts p0;
   MxProducts* const p[1] = {&p0};
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks) {
-    const MxOperand b0 = mx_split(x + 8 * ks);
+    const MxOperand b0 = mx_split<FIRST>(x + 8 * ks);
     const MxOperand* const b[1] = {&b0};
     mx_products<1>(b, fr, ks, p);
   }
   mx_write<PAIRS>(g, p0, g.out0, tile);
+  return p0.im[0] != p0.im[0];
 }
 
-// The stages of a complex64 matrix pass.  Column bit j of a stage is local
-// bit colimg[j]: lane bits first, then wave bits; wave w owns the column
-// blocks w and w + 4 and overwrites them in place, so stages without
-// kMatrixStageSync (which keep every element with its wave) need no barrier.
-__device__ __forceinline__ void matrix_stages(const TileRef<float>& T, flt2* tile) {
-  constexpr int LB = 1, NW = kBlock / 64;
+template <bool PAIRS, bool FIRST>
+__device__ __forceinline__ bool mx_stage(bool two, const MxGeo& g, gptr<const u32x4> fr, flt2* tile) {
+  return two ? mx_stage_two<PAIRS, FIRST>(g, fr, tile) : mx_stage_one<PAIRS, FIRST>(g, fr, tile);
+}
+
+// Offsets of stage S for wave w of a tile of 2^m amplitudes.  Column bit j of a
+// stage is local bit colimg[j]: lane bits first, then wave bits.
+__device__ __forceinline__ MxGeo mx_geo(cptr<PassStageDev> S, uint32_t m, uint32_t w) {
+  constexpr int LB = 1;
+  const uint32_t l = threadIdx.x & 63u;
+  MxGeo g;
+#pragma unroll
+  for (int b = 0; b < 5; ++b) g.sb[b] = swz<LB>(1u << S->q[b]);
+  uint32_t col = 0;  // the lane's column bits
+#pragma unroll
+  for (int j = 0; j < 5; ++j) col ^= ((l >> j) & 1u) ? swz<LB>(1u << S->colimg[j]) : 0u;
+  uint32_t wc[3];  // column block bits
+#pragma unroll
+  for (int j = 0; j < 3; ++j) wc[j] = 5u + j < m - 5u ? swz<LB>(1u << S->colimg[5 + j]) : 0u;
+  col ^= ((w & 1u) ? wc[0] : 0u) ^ ((w & 2u) ? wc[1] : 0u);
+  g.in0 = col ^ (l >= 32u ? g.sb[3] : 0u);
+  g.out0 = col ^ (l >= 32u ? g.sb[2] : 0u);
+  g.next = wc[2];
+  return g;
+}
+
+// The stages of a complex64 matrix pass.  Wave w owns the column blocks w and
+// w + 4 and overwrites them in place, so stages without kMatrixStageSync
+// (which keep every element with its wave) need no barrier.  A tile with
+// values that the split cannot hold (amplitudes from 2^112 or not finite,
+// matrix entries that are not finite, overflow beside small entries) leaves
+// results that are not numbers: some lane of the last stage sees one and writes
+// the tile's number `id` (nonzero, of its own) to *redo; the caller then runs
+// matrix_stages_fp32.
+__device__ __forceinline__ void matrix_stages(const TileRef<float>& T, flt2* tile, uint32_t id, uint32_t* redo) {
+  constexpr int NW = kBlock / 64;
   const cptr<PassDescDev> P = T.P;
   const uint32_t m = P->m, ns = P->stage_count;
   const uint32_t l = threadIdx.x & 63u;
   const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t cblocks = 1u << (m - 10u);
+  bool bad = false;
   for (uint32_t si = 0; si < ns; ++si) {
     const cptr<PassStageDev> S = T.stages + (P->stage_first + si);
     if (si > 0) {
@@ -1030,28 +1151,38 @@ __device__ __forceinline__ void matrix_stages(const TileRef<float>& T, flt2* til
         asm volatile("" ::: "memory");
       }
     }
-    const gptr<const u32x4> fr = as_global(reinterpret_cast<const u32x4*>(T.frags)) + (size_t)S->mx * (kStageFragBytes / 16) + l;
-    MxGeo g;
-#pragma unroll
-    for (int b = 0; b < 5; ++b) g.sb[b] = swz<LB>(1u << S->q[b]);
-    uint32_t col = 0;  // the lane's column bits
-#pragma unroll
-    for (int j = 0; j < 5; ++j) col ^= ((l >> j) & 1u) ? swz<LB>(1u << S->colimg[j]) : 0u;
-    uint32_t wc[3];  // column block bits
-#pragma unroll
-    for (int j = 0; j < 3; ++j) wc[j] = 5u + j < m - 5u ? swz<LB>(1u << S->colimg[5 + j]) : 0u;
-    col ^= ((w & 1u) ? wc[0] : 0u) ^ ((w & 2u) ? wc[1] : 0u);
-    g.in0 = col ^ (l >= 32u ? g.sb[3] : 0u);
-    g.out0 = col ^ (l >= 32u ? g.sb[2] : 0u);
-    g.next = wc[2];
+    const uint32_t mx = S->mx;
+    const gptr<const u32x4> fr = mx_frags(T.frags, mx) + l;
+    const bool first = si == 0;
+    const MxGeo g = mx_geo(S, m, w);
     const bool pairs = S->q[0] == 0;
-    if (cblocks == 2 * NW) {
-      if (pairs) mx_stage_two<true>(g, fr, tile);
-      else mx_stage_two<false>(g, fr, tile);
-    } else if (w < cblocks) {  // a small tile: one column block per wave
-      if (pairs) mx_stage_one<true>(g, fr, tile);
-      else mx_stage_one<false>(g, fr, tile);
+    const bool two = cblocks == 2 * NW;  // (else a small tile: one column block per wave)
+    if (first) bad = pairs ? mx_stage<true, true>(two, g, fr, tile) : mx_stage<false, true>(two, g, fr, tile);
+    else bad = pairs ? mx_stage<true, false>(two, g, fr, tile) : mx_stage<false, false>(two, g, fr, tile);
+    if (__builtin_expect((mx & kFragSmallEntries) != 0, 0)) {
+      wait_lgkm0();  // (the wave's own results)
+#pragma unroll 1
+      for (uint32_t cb = w; cb < cblocks; cb += NW) bad |= mx_unscale_block(g, g.out0 ^ (cb != w ? g.next : 0u), tile);
     }
+  }
+  if (bad) *redo = id;
+  lds_sync();
+}
+// The tile once more, from memory and in FP32 (no lane reads the tile any more).
+__device__ __forceinline__ void matrix_stages_fp32(const TileRef<float>& T, flt2* tile) {
+  constexpr int NW = kBlock / 64;
+  const cptr<PassDescDev> P = T.P;
+  const uint32_t m = P->m, ns = P->stage_count;
+  const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t cblocks = 1u << (m - 10u);
+  tile_load_lds<float>(T, tile);
+  wait_vm<0>();
+  for (uint32_t si = 0; si < ns; ++si) {
+    lds_sync();
+    const cptr<PassStageDev> S = T.stages + (P->stage_first + si);
+    const MxGeo g = mx_geo(S, m, w);
+#pragma unroll 1
+    for (uint32_t cb = w; cb < cblocks; cb += NW) mx_stage_fp32(g, T.mats + S->u2, g.out0 ^ (cb != w ? g.next : 0u), tile);
   }
   lds_sync();
 }
@@ -1156,7 +1287,7 @@ __device__ __forceinline__ void tile_stages(const TileRef<R>& T, typename dev_el
       if constexpr (MX == MX_NONE) {
         register_part(S);
       } else if (S.mx() != kPassNoTable) {
-        folded = mx_apply(v, as_global(reinterpret_cast<const u32x4*>(T.frags)) + (size_t)S.mx() * (kStageFragBytes / 16));
+        if (!(S.mx() & kFragSmallEntries)) folded = mx_apply(v, T.frags, S.mx());
         if (__builtin_expect(!folded, 0)) {
           // the tile still holds the wave's amplitudes (opaque copies: what
           // this rare branch needs does not occupy registers before it)
@@ -1314,14 +1445,6 @@ __device__ __forceinline__ void put_one(const TileRef<R>& T, const PutMap<R>& p,
   stg<G>(gpsi + (ad >> gelem<R>::LB), v);
 }
 
-// s_waitcnt with only the vector-memory counter (gfx9 encoding: expcnt and
-// lgkmcnt at their no-wait values).
-template <int N>
-__device__ __forceinline__ void wait_vm() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
-}
-
 // Moves of a full tile (64 KiB: 16 elements per lane) are straight-line code,
 // those of a smaller tile a loop, and lanes without a group read group 0
 // instead of skipping their LDS reads: with a predicate per element every
@@ -1346,6 +1469,8 @@ __device__ __forceinline__ void tile_loop(uint64_t total, const Src& src, typena
   if (g >= total) return;
   tile_load_lds<R>(src(g), tile);
   bool full_prev = false;  // the previous tile's kBatch stores per lane follow the loads
+  __shared__ uint32_t redo;  // the tile that a matrix pass computes again
+  if (MX == MX_ONLY && threadIdx.x == 0) redo = 0;
   while (true) {
     const uint64_t ng = g + gridDim.x;
     const TileRef<R> cur = src(g);
@@ -1355,19 +1480,31 @@ __device__ __forceinline__ void tile_loop(uint64_t total, const Src& src, typena
     if (full_prev) wait_vm<kBatch>();
     else wait_vm<0>();
     lds_barrier();
-    if constexpr (MX == MX_ONLY) matrix_stages(cur, tile);
+    [[maybe_unused]] const uint32_t id = (uint32_t)g + 1u;
+    if constexpr (MX == MX_ONLY) matrix_stages(cur, tile, id, &redo);
     else tile_stages<R, LP, MX>(cur, tile, pre, npre);
     const LaneGeo lg = lane_geo<gelem<R>::LB>(cur.P->m);
     full_prev = lg.full;
     if (lg.full) {
       G out[kBatch];
       const GatherMap<R> gm = gather_map<R>(cur.P);
-      if (gm.lane_order) {
+      auto gather = [&]() {
+        // (two arms, so that the order is a constant in each)
+        if (gm.lane_order) {
 #pragma unroll
-        for (int u = 0; u < kBatch; ++u) out[u] = gather_one<R>(gm, tile, u);
-      } else {
+          for (int u = 0; u < kBatch; ++u) out[u] = gather_one<R>(gm, tile, u);
+        } else {
 #pragma unroll
-        for (int u = 0; u < kBatch; ++u) out[u] = gather_one<R>(gm, tile, u);
+          for (int u = 0; u < kBatch; ++u) out[u] = gather_one<R>(gm, tile, u);
+        }
+      };
+      gather();
+      if constexpr (MX == MX_ONLY) {  // (read beside the tile: the wait is the gather's)
+        if (__builtin_expect(__builtin_amdgcn_readfirstlane(redo) == id, 0)) {
+          lds_sync();
+          matrix_stages_fp32(cur, tile);
+          gather();
+        }
       }
       wait_lgkm0();  // this lane's LDS reads are done
       lds_barrier();
@@ -1377,6 +1514,11 @@ __device__ __forceinline__ void tile_loop(uint64_t total, const Src& src, typena
 #pragma unroll
       for (int u = 0; u < kBatch; ++u) put_one<R>(cur, pm, u, out[u]);
     } else {  // a small tile: element by element
+      if constexpr (MX == MX_ONLY)
+        if (__builtin_expect(__builtin_amdgcn_readfirstlane(redo) == id, 0)) {
+          lds_sync();
+          matrix_stages_fp32(cur, tile);
+        }
       const GatherMap<R> gm = gather_map<R>(cur.P);
       const PutMap<R> pm = put_map<R>(cur);
       if (lg.on) {
@@ -1832,7 +1974,7 @@ hipError_t launch_matrix_pass(int k, void* psi, int n, int m, const PassDescDev*
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_stage_frags(const PassStageDev* stages, const uint32_t* list, int count, const void* pool,
+hipError_t launch_stage_frags(PassStageDev* stages, const uint32_t* list, int count, const void* pool,
                               void* frags, hipStream_t s) {
   hipLaunchKernelGGL(k_stage_frags, dim3((unsigned)count), dim3(kBlock), 0, s, stages, list, (const cplx<float>*)pool,
                      (uint32_t*)frags);

@@ -685,7 +685,8 @@ sv_status pack_plan(const sv_plan* p, PackedPlan* out) {
       sd.mx = kPassNoTable;
       if (out->pass_mx[i] == kPassMatrixOnly || (out->pass_mx[i] == kPassMatrixTile && stage_has_layers(sh))) {
         sd.mx = (uint32_t)mx_list.size();
-        mx_list.push_back((uint32_t)stages.size() | (ps.kind == PASS_MATRIX ? kFragMatrixStage : 0u));
+        mx_list.push_back((uint32_t)stages.size() | (ps.kind == PASS_MATRIX ? kFragMatrixStage : 0u) |
+                          (ps.kind == PASS_MATRIX && &sh == &ps.stages.back() ? kFragLastStage : 0u));
       }
       sd.px_first = (uint32_t)items.size();
       sd.px_count = (uint32_t)sh.px.size();

@@ -160,9 +160,13 @@ struct alignas(16) PassStageDev {
 // (launch_stage_frags) after the program has been uploaded.
 constexpr int kStageFragBytes = 32 * 32 * 2 * 3 * 2;
 // List entry of launch_stage_frags: a stage index; kFragMatrixStage is set
-// for a stage of a matrix pass (a 32 x 32 matrix at pool entry u2).
-constexpr uint32_t kFragMatrixStage = 0x80000000u;
-hipError_t launch_stage_frags(const PassStageDev* stages, const uint32_t* list, int count, const void* pool,
+// for a stage of a matrix pass (a 32 x 32 matrix at pool entry u2), and
+// kFragLastStage for its last one.
+constexpr uint32_t kFragMatrixStage = 0x80000000u, kFragLastStage = 0x40000000u, kFragStage = 0x3fffffffu;
+// Set by the device in a stage's `mx`: its matrix has nonzero entries too small
+// for the usual scale of the fragments (sv_pass.hip, kMxSmallEntry).
+constexpr uint32_t kFragSmallEntries = 0x80000000u;
+hipError_t launch_stage_frags(PassStageDev* stages, const uint32_t* list, int count, const void* pool,
                               void* frags, hipStream_t s);
 
 // PassDescDev flag: the store can walk the tile in load order (the lowest

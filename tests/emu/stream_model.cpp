@@ -133,7 +133,7 @@ hipError_t launch_pass(sv_dtype, void*, int, int, const PassDescDev* passes, int
   enqueue("a pass", {span(passes + pass, sizeof(PassDescDev))});
   return hipSuccess;
 }
-hipError_t launch_stage_frags(const PassStageDev* stages, const uint32_t* list, int count, const void* pool, void* frags,
+hipError_t launch_stage_frags(PassStageDev* stages, const uint32_t* list, int count, const void* pool, void* frags,
                               hipStream_t) {
   enqueue("the fragment build", {span(list, count * sizeof(uint32_t)), span(stages, sizeof(PassStageDev)),
                                  span(pool, 16), span(frags, (size_t)count * kStageFragBytes)});
