@@ -285,6 +285,17 @@ double matrix_pass_cost(sv_dtype dt, int k, int stages) {
   return 0.65 + 0.84 * stages * (double)(1 << k) / 32.0;
 }
 
+// Cost of building the fragments of a complex64 plan's matrix stages, in
+// full-state sweeps: a launch of its own, 8 us with the gap before it; a sweep
+// takes 4 us at least.  Without it circuits of a few gates on small states got
+// matrix passes that lose: N = 13, a 3-qubit unitary between two single-qubit
+// gates, 41 us against 20 for a tile pass and a dense sweep; N = 20, 29 gates,
+// 80 against 71 us.
+double fragment_build_cost(int n) {
+  const double sweep_us = std::ldexp(16.0, n) / 6.5e6;
+  return 8.0 / std::max(sweep_us, 4.0);
+}
+
 // Bank class of local bit b in the kernels' LDS layout: the low bits of the
 // swizzled index of amplitude 2^b inside a 128-byte row (sv_pass.hip, swz;
 // complex64 rows hold 16 amplitudes, complex128 rows 8).
@@ -378,6 +389,7 @@ double plan_matrix_passes(const std::vector<Op>& fused, int n, sv_dtype dt, cons
   }
   std::vector<char> done(fused.size(), 0);
   size_t first = 0;
+  bool any_matrix = false;
   auto emit_sweep = [&](const Op& op) {
     est_cost += sweep_cost(op, dt, mfma);
     if (!p) return;
@@ -435,6 +447,7 @@ double plan_matrix_passes(const std::vector<Op>& fused, int n, sv_dtype dt, cons
       continue;
     }
     est_cost += cost;
+    any_matrix = true;
     for (size_t j : members) done[j] = 1;
     if (!p) continue;
     // the tile: the group's qubits, the pinned bits, then the lowest others
@@ -504,6 +517,7 @@ double plan_matrix_passes(const std::vector<Op>& fused, int n, sv_dtype dt, cons
     assign_matrix_columns(ps, dt);
     p->passes.push_back(std::move(ps));
   }
+  if (any_matrix && dt == SV_C64) est_cost += fragment_build_cost(n);
   if (p) p->est_cost = est_cost;
   return est_cost;
 }
