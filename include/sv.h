@@ -292,7 +292,7 @@ const char *sv_last_error(void);
  * step per pass (continuous batching): one kernel launch runs the next
  * in-cache tile pass of every active state, so requests admitted later join
  * the next launch and their work overlaps with older ones on the device
- * (passes that need another variant of the kernel share a launch of theirs);
+ * (complex64 matrix passes share a launch of theirs);
  * a state whose next pass is a dense, sweep or complex128 matrix pass runs it
  * as a launch of its own in the same step. */
 typedef struct sv_program sv_program;  /* the passes of one plan, in device memory */
@@ -333,9 +333,9 @@ sv_status sv_program_destroy(sv_program *prog);
 sv_status sv_batcher_create(void *hip_stream, sv_batcher **out);
 
 /* One step: for every i < count, run pass pass_index[i] of programs[i] on
- * states[i] -- the tile, permutation and complex64 matrix passes of all items
- * in one launch per kernel variant they need, each complex128 matrix, dense or
- * sweep pass in a launch of its own.  All states and programs must share one dtype; states[i] must
+ * states[i] -- the tile and permutation passes of all items in one launch,
+ * complex64 matrix passes in another, each complex128 matrix, dense or sweep
+ * pass in a launch of its own.  All states and programs must share one dtype; states[i] must
  * have programs[i]'s qubit count; a state may appear at most once.  Work is
  * enqueued on the batcher's stream: the caller orders it against other work
  * on the states (e.g. by creating the states on the same stream).  A state's

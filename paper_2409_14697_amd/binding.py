@@ -419,9 +419,9 @@ class Program:
 
 
 class Batcher:
-    """One step runs one pass of many states (sv_batcher_*): their tile,
-    permutation and complex64 matrix passes in one launch per kernel variant,
-    dense, sweep and complex128 matrix passes as launches of their own."""
+    """One step runs one pass of many states (sv_batcher_*): their tile and
+    permutation passes in one launch, complex64 matrix passes in another, dense,
+    sweep and complex128 matrix passes as launches of their own."""
 
     def __init__(self, stream=None):
         import torch

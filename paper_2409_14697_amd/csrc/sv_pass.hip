@@ -1191,8 +1191,9 @@ __device__ __forceinline__ void matrix_stages_fp32(const TileRef<float>& T, flt2
 // pass holds fixed-point phase items.  MX_NONE: the register parts of its
 // stages run on the VALU; MX_TILE: on the matrix cores (and on the VALU in
 // waves whose amplitudes the split cannot hold); MX_ONLY: a matrix pass, whose
-// stages are matrices and nothing else.
-enum { MX_NONE = 0, MX_TILE = 1, MX_ONLY = 2 };
+// stages are matrices and nothing else; MX_MIXED: MX_NONE or MX_TILE, as the
+// tile's pass says.
+enum { MX_NONE = 0, MX_TILE = 1, MX_ONLY = 2, MX_MIXED = 3 };
 
 template <typename R, bool LP, int MX>
 __device__ __forceinline__ void tile_stages(const TileRef<R>& T, typename dev_elem<R>::E* tile,
@@ -1482,7 +1483,10 @@ __device__ __forceinline__ void tile_loop(uint64_t total, const Src& src, typena
     lds_barrier();
     [[maybe_unused]] const uint32_t id = (uint32_t)g + 1u;
     if constexpr (MX == MX_ONLY) matrix_stages(cur, tile, id, &redo);
-    else tile_stages<R, LP, MX>(cur, tile, pre, npre);
+    // (code of its own for either: a pass rounds as it does in a launch alone)
+    else if constexpr (MX != MX_MIXED) tile_stages<R, LP, MX>(cur, tile, pre, npre);
+    else if (cur.P->flags & kPassMatrixStages) tile_stages<R, LP, MX_TILE>(cur, tile, pre, npre);
+    else tile_stages<R, LP, MX_NONE>(cur, tile, pre, npre);
     const LaneGeo lg = lane_geo<gelem<R>::LB>(cur.P->m);
     full_prev = lg.full;
     if (lg.full) {
@@ -2000,6 +2004,9 @@ hipError_t launch_pass_batch(sv_dtype dt, const BatchItemDev* items, int count, 
   if (mx == kPassMatrixTile)
     return ladders ? run_batch<float, true, MX_TILE>(items, count, total_tiles, max_m, s)
                    : run_batch<float, false, MX_TILE>(items, count, total_tiles, max_m, s);
+  if (mx == kPassMatrixMixed)
+    return ladders ? run_batch<float, true, MX_MIXED>(items, count, total_tiles, max_m, s)
+                   : run_batch<float, false, MX_MIXED>(items, count, total_tiles, max_m, s);
   return ladders ? run_batch<float, true, MX_NONE>(items, count, total_tiles, max_m, s)
                  : run_batch<float, false, MX_NONE>(items, count, total_tiles, max_m, s);
 }

@@ -664,6 +664,7 @@ sv_status pack_plan(const sv_plan* p, PackedPlan* out) {
         if (ps.wpos[j] != ps.lpos[j]) return fail(SV_ERR_UNSUPPORTED, "internal: matrix pass with a write map");
     if (f32 && ps.kind == PASS_MATRIX) out->pass_mx[i] = kPassMatrixOnly;
     else if (pass_on_matrix_cores(ps.stages, p->dt, p->opts)) out->pass_mx[i] = kPassMatrixTile;
+    if (out->pass_mx[i] == kPassMatrixTile) d.flags |= kPassMatrixStages;
     for (const StageHost& sh : ps.stages) {
       PassStageDev sd{};
       // register bits of a tile stage, members of a matrix stage

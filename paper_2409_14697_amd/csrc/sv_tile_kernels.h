@@ -173,11 +173,13 @@ hipError_t launch_stage_frags(PassStageDev* stages, const uint32_t* list, int co
 // three 16-byte element bits keep their positions, so every run of 8 lanes
 // still writes 128 contiguous bytes); otherwise it walks destination order.
 constexpr uint32_t kPassStoreLaneOrder = 1;
+// PassDescDev flag: the pass has matrix stages (kPassMatrixTile).
+constexpr uint32_t kPassMatrixStages = 2;
 
 struct alignas(16) PassDescDev {
   uint32_t m;                    // local bits per tile
   uint32_t stage_first, stage_count;
-  uint32_t flags;                // kPassStoreLaneOrder
+  uint32_t flags;                // kPassStoreLaneOrder, kPassMatrixStages
   uint64_t lmask;                // physical mask of the local bits
   uint32_t lpos[16];             // physical position of local bit j on load (ascending)
   uint32_t wpos[16];             // physical position of local bit j on store (a permutation of lpos)
@@ -200,11 +202,12 @@ struct alignas(16) BatchItemDev {
 // Where a complex64 pass runs the register parts of its stages: on the VALU,
 // on the matrix cores (every stage with a register part has an `mx` entry), or
 // on the matrix cores as the whole stage (a matrix pass).
-enum PassMatrix : char { kPassMatrixNone = 0, kPassMatrixTile = 1, kPassMatrixOnly = 2 };
+enum PassMatrix : char { kPassMatrixNone = 0, kPassMatrixTile = 1, kPassMatrixOnly = 2, kPassMatrixMixed = 3 };
 
 // Run pass items[i].pass of every item in one launch; all items share dt and
-// mx.  ladders: some item's pass holds PIT_LP or PIT_QG items.  (Both select
-// the kernel variant that holds the code the passes need.)
+// mx (kPassMatrixMixed: passes of kPassMatrixNone and kPassMatrixTile).
+// ladders: some item's pass holds PIT_LP or PIT_QG items.  (Both select the
+// kernel variant that holds the code the passes need.)
 hipError_t launch_pass_batch(sv_dtype dt, const BatchItemDev* items, int count, uint64_t total_tiles, int max_m,
                              bool ladders, PassMatrix mx, hipStream_t s);
 

@@ -33,6 +33,7 @@ std::vector<size_t> pinned_sizes;
 int faults = 0;
 int fail_launch = -1;  // the batched launch (counted from 0) that fails
 int batch_launches = 0;
+uint64_t batch_tiles = 0;
 
 void fault(const std::string& s) {
   std::printf("%s\n", s.c_str());
@@ -139,9 +140,13 @@ hipError_t launch_stage_frags(PassStageDev* stages, const uint32_t* list, int co
                                  span(pool, 16), span(frags, (size_t)count * kStageFragBytes)});
   return hipSuccess;
 }
-hipError_t launch_pass_batch(sv_dtype, const BatchItemDev* items, int count, uint64_t, int, bool, PassMatrix,
+hipError_t launch_pass_batch(sv_dtype, const BatchItemDev* items, int count, uint64_t tiles, int, bool, PassMatrix,
                              hipStream_t) {
   if (batch_launches++ == fail_launch) return hipErrorInvalidValue;
+  for (int i = 1; i < count; ++i)
+    if (items[i].tile_begin <= items[i - 1].tile_begin || items[i].tile_begin >= tiles) fault("tile ranges out of order");
+  if (items[0].tile_begin != 0) fault("the first item does not start at tile 0");
+  batch_tiles += tiles;
   enqueue("a batched pass", {span(items, count * sizeof(BatchItemDev))});
   return hipSuccess;
 }
@@ -211,12 +216,7 @@ void scenario_program() {
 // enqueued are still read when its slot comes round again.
 void scenario_batcher() {
   const int n = 13;
-  sv_gate g[2] = {gate(SV_G_RY, {3}, 0.2), gate(SV_G_RX, {8}, 0.4)};
-  sv_opts o;
-  sv_default_opts(&o);
-  o.mode = SV_MODE_PASS;
-  sv_plan* plans[2] = {plan(n, SV_MODE_PASS, 5), nullptr};  // on the matrix cores, on the VALU
-  expect(sv_fuse(n, SV_C64, g, 2, &o, &plans[1]), SV_OK);
+  sv_plan* plans[2] = {plan(n, SV_MODE_PASS, 5), plan(n, SV_MODE_MATRIX, 5)};  // tile stages, matrix stages
   sv_program* progs[2];
   sv_state* states[2];
   for (int i = 0; i < 2; ++i) {
@@ -225,7 +225,12 @@ void scenario_batcher() {
   }
   sv_batcher* b = nullptr;
   expect(sv_batcher_create(nullptr, &b), SV_OK);
-  const int32_t pass[2] = {0, 0};
+  int32_t pass[2] = {0, -1};
+  for (int32_t k = 0, kind, ops, local, stages; pass[1] < 0; ++k) {
+    expect(sv_plan_pass_info(plans[1], (size_t)k, &kind, &ops, &local, &stages), SV_OK);
+    if (faults) return;
+    if (kind == sv::PASS_MATRIX) pass[1] = k;
+  }
   for (int failing = 0; failing < 2; ++failing) {
     batch_launches = 0;
     fail_launch = failing;
@@ -239,6 +244,38 @@ void scenario_batcher() {
     expect(sv_program_destroy(progs[i]), SV_OK);
     expect(sv_destroy(states[i]), SV_OK);
     sv_plan_destroy(plans[i]);
+  }
+}
+
+// Tile passes with and without matrix stages run in one launch.
+void scenario_launches() {
+  for (int n : {13, 22}) {  // one tile, 512 tiles
+    sv_gate g[2] = {gate(SV_G_RY, {3}, 0.2), gate(SV_G_RX, {8}, 0.4)};
+    sv_opts o;
+    sv_default_opts(&o);
+    o.mode = SV_MODE_PASS;
+    sv_plan* plans[2] = {plan(n, SV_MODE_PASS, 5), nullptr};  // on the matrix cores, on the VALU
+    expect(sv_fuse(n, SV_C64, g, 2, &o, &plans[1]), SV_OK);
+    sv_program* progs[2];
+    sv_state* states[2];
+    for (int i = 0; i < 2; ++i) {
+      expect(sv_program_create(plans[i], nullptr, 0, nullptr, &progs[i]), SV_OK);
+      expect(sv_create(n, SV_C64, nullptr, nullptr, SV_NO_INIT, &states[i]), SV_OK);
+    }
+    sv_batcher* b = nullptr;
+    expect(sv_batcher_create(nullptr, &b), SV_OK);
+    const int32_t pass[2] = {0, 0};
+    batch_launches = 0;
+    batch_tiles = 0;
+    expect(sv_batcher_run(b, 2, states, progs, pass), SV_OK);
+    if (batch_launches != 1) fault("N = " + std::to_string(n) + ": " + std::to_string(batch_launches) + " launches");
+    if (batch_tiles != (2ull << (n - 13))) fault("N = " + std::to_string(n) + ": " + std::to_string(batch_tiles) + " tiles");
+    expect(sv_batcher_destroy(b), SV_OK);
+    for (int i = 0; i < 2; ++i) {
+      expect(sv_program_destroy(progs[i]), SV_OK);
+      expect(sv_destroy(states[i]), SV_OK);
+      sv_plan_destroy(plans[i]);
+    }
   }
 }
 
@@ -278,6 +315,7 @@ int main(int argc, char** argv) {
   const std::string s = argc > 1 ? argv[1] : "";
   if (s == "program") scenario_program();
   else if (s == "batcher") scenario_batcher();
+  else if (s == "launches") scenario_launches();
   else if (s == "staging") scenario_staging();
   else fault("unknown scenario");
   return faults ? 1 : 0;

@@ -5,7 +5,8 @@ import numpy as np
 import pytest
 
 import oracle
-from svgen import Gate, gaussian_state_np, haar_unitary
+from svgen import (Gate, brickwork_circuit, gaussian_state_np, haar_unitary, layered_circuit, qaoa_circuit,
+                   qft_circuit)
 from tests.gpu_util import to_device, to_host
 
 pytestmark = pytest.mark.gpu
@@ -97,3 +98,30 @@ def test_not_finite_reaches_what_the_gates_mix(sv, n, lds, value):
         assert np.all(np.isfinite(out[~group].real) & np.isfinite(out[~group].imag))
         ref = oracle.run(gates, psi0=clean.astype(np.complex64).astype(np.complex128))
         assert np.max(np.abs(out[~group] - ref[~group])) <= 1e-6
+
+
+@pytest.mark.parametrize("n,lds", [(8, 0), (10, 0), (13, 0), (13, 9), (15, 0)])
+def test_mixed_steps_share_a_launch(sv, n, lds):
+    """Passes with and without matrix stages in one step: every state as its plan
+    leaves it alone, bit for bit."""
+    circuits = [qft_circuit(n), layered_circuit(n, n_gates=6 * n, seed=2), qaoa_circuit(n, 1, seed=3),
+                [Gate("X", (0,)), Gate("CNOT", (1, 4)), Gate("SWAP", (2, n - 1))], brickwork_circuit(n, 4, seed=1)]
+    states, programs, alone, extra = [], [], [], []
+    for i, gates in enumerate(circuits):
+        plan = sv.Plan(n, "c64", gates, {"mode": "pass", "lds_qubits": lds})
+        extra.append(tile_plans(sv, n, gates, lds)[2])
+        for out in (alone, states):
+            t, _ = to_device(gaussian_state_np(n, i), "c64")
+            s = sv.StateVector(n, "c64", tensor=t, init=False)
+            out.append(s)
+        alone[-1].apply_plan(plan)
+        programs.append(sv.Program(plan))
+    assert extra[0] > 0 and extra[1] == 0
+    b = sv.Batcher()
+    for k in range(max(p.n_passes for p in programs)):
+        act = [i for i, p in enumerate(programs) if k < p.n_passes]
+        b.run([states[i] for i in act], [programs[i] for i in act], [k] * len(act))
+    for s, a in zip(states, alone):
+        s.sync()
+        a.sync()
+        assert np.array_equal(to_host(s.tensor), to_host(a.tensor))

@@ -23,7 +23,7 @@ def model(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("scenario", ["program", "batcher", "staging"])
+@pytest.mark.parametrize("scenario", ["program", "batcher", "staging", "launches"])
 def test_queued_work(model, scenario):
     r = subprocess.run([model, scenario], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout + r.stderr
