@@ -99,9 +99,10 @@ bool finite_matrix(const std::vector<cd>& m) {
 // `g`: every column is treated as a k-qubit vector and g is applied to the
 // groups of its positions (Eq. 2/3 on the fused space).  sparse: the rows of
 // a phase or permutation gate are scaled or exchanged (one or two of four
-// rows of a controlled gate) instead of multiplied by its zeros and ones; the
-// products are the same as long as every entry is finite, which the caller
-// knows.
+// rows of a controlled gate) instead of multiplied by its zeros and ones.  The
+// caller knows that every entry it was given is finite; an entry of a product
+// that overflows is then moved as it is instead of spread as zero times
+// infinity.
 void apply_left(std::vector<cd>& m, int k, const int* uq, const Op& g, bool sparse) {
   const int d = 1 << k;
   const int dg = 1 << g.nq;
