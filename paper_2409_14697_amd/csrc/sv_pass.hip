@@ -1495,22 +1495,20 @@ __device__ __forceinline__ void tile_loop(uint64_t total, const Src& src, typena
     if (lg.full) {
       G out[kBatch];
       const GatherMap<R> gm = gather_map<R>(cur.P);
-      auto gather = [&]() {
-        // (two arms, so that the order is a constant in each)
-        if (gm.lane_order) {
+      // (two arms, so that the order is a constant in each)
+      if (gm.lane_order) {
 #pragma unroll
-          for (int u = 0; u < kBatch; ++u) out[u] = gather_one<R>(gm, tile, u);
-        } else {
+        for (int u = 0; u < kBatch; ++u) out[u] = gather_one<R>(gm, tile, u);
+      } else {
 #pragma unroll
-          for (int u = 0; u < kBatch; ++u) out[u] = gather_one<R>(gm, tile, u);
-        }
-      };
-      gather();
+        for (int u = 0; u < kBatch; ++u) out[u] = gather_one<R>(gm, tile, u);
+      }
       if constexpr (MX == MX_ONLY) {  // (read beside the tile: the wait is the gather's)
         if (__builtin_expect(__builtin_amdgcn_readfirstlane(redo) == id, 0)) {
           lds_sync();
           matrix_stages_fp32(cur, tile);
-          gather();
+#pragma unroll
+          for (int u = 0; u < kBatch; ++u) out[u] = gather_one<R>(gm, tile, u);
         }
       }
       wait_lgkm0();  // this lane's LDS reads are done
