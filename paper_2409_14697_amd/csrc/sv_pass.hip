@@ -289,8 +289,9 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // with smaller nonzero entries is marked (kFragSmallEntries): a tile stage then
 // runs on the VALU, a matrix stage has fragments 2^32 times as large and scales
 // its results back, which must stay finite.  Measured: 64 VALU instructions more
-// per wave and scaling stage, QFT N = 28 6.81 -> 6.89 ms; brickwork N = 30 stays
-// at 136 ms (138 with a scaling in every stage of a pass).
+// per wave and scaling stage, QFT N = 28 6.76 -> 6.83 ms (6.78 since its lane
+// factors skip products with 1); brickwork N = 30 stays at 136 ms (138 with a
+// scaling in every stage of a pass).
 constexpr float kMxScale = 0x1p16f, kMxUnscale = 0x1p-16f;
 constexpr float kMxSmallScale = 0x1p32f, kMxSmallUnscale = 0x1p-32f;
 constexpr double kMxSmallEntry = 0x1p-94;
@@ -785,10 +786,13 @@ __device__ __forceinline__ void lane_diag(const Stage& S, cptr<PassItemDev> item
   }
   if (folded) {  // the register factors are part of the stage's matrix
 #pragma unroll
-    for (int r = 0; r < HALF; ++r) {
-      v[r] = cmul(cmul(H[r], f0[RB - 1]), v[r]);
-      v[r + HALF] = cmul(cmul(H[r], f1[RB - 1]), v[r + HALF]);
+    for (int r = 0; r < HALF; ++r) v[r + HALF] = cmul(cmul(H[r], f1[RB - 1]), v[r + HALF]);
+    if (S.flags() & PSF_F0) {  // (else f0 is 1: 16 products that the stage's scaling costs)
+#pragma unroll
+      for (int r = 0; r < HALF; ++r) H[r] = cmul(H[r], f0[RB - 1]);
     }
+#pragma unroll
+    for (int r = 0; r < HALF; ++r) v[r] = cmul(H[r], v[r]);
     return;
   }
   const cptr<cplx<R>> D = mats + S.dr();
